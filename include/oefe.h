@@ -240,13 +240,10 @@ size_t oefe_batched_work_size(int32_t nk, const oefe_op* ops, oefe_prec prec, co
  * 0 (built-in) puts the (p+1) planes of a cell tensor in the lanes of one wave
  * (64/(p+1) columns, rounded down to even, per wave); 8, 16, 32 or 64 put one
  * plane per wave with cw real columns per cell in a 64-lane tile (64/cw cells).
- * cb (a multiple of 16 up to 128; 0 = built-in) is the real-column width of one
- * unit of the node stage: the workgroup of the fused node kernel of a real
- * operator (at most 80 columns are used: built-in, all columns up to 80, else
- * near-equal blocks), or one
- * wave of the coupling kernel (the H^co products) of a Bloch operator, where 16
- * and 32 are used (larger values act as 32; built-in 16).  Results do not depend
- * on the shape. */
+ * cb (a multiple of 16 up to 128; 0 = built-in) is the width of a workgroup of the
+ * node stage in column groups: cb / 16 groups of 16 real columns (float32: 32),
+ * of which 1, 2 and 4 are used (3 acts as 2, more as 4; built-in: the widest
+ * occupancy).  Results do not depend on the shape. */
 int oefe_set_launch_shape(oefe_op op, int32_t cw, int32_t cb);
 
 /* Autotuner of the launch shape for a batch of operators (nk >= 1, same rules
@@ -412,11 +409,9 @@ int oefe_poisson_solve_adaptive(oefe_op pop, const double* rho, const double* rh
 /* Instrumentation.  While a kernel is selected, each of its launches inside
  * ham_apply / chebyshev_filter* is bracketed by HIP events on the stream it is
  * launched on.  which: OEFE_TIMER_OFF, OEFE_TIMER_CELL (the sum-factorized
- * H^cc cell stage), OEFE_TIMER_NODE (the node stage on the main stream: for a
- * real operator the fused kernel with the slot gather, the H^co products and the
- * recurrence epilogue; for a Bloch operator the node assembly, slot gather and
- * epilogue) or OEFE_TIMER_COUPLING (the H^co products of a Bloch operator, on
- * the filter's side stream).  oefe_kernel_timer_read
+ * H^cc cell stage), OEFE_TIMER_NODE (the node stage: the slot gather, the H^co
+ * products and the recurrence epilogue in one kernel) or OEFE_TIMER_COUPLING (the
+ * same kernel, of a Bloch operator only).  oefe_kernel_timer_read
  * synchronizes, returns the number of bracketed launches and their summed
  * duration (ms), and clears the record.  Selecting a kernel discards events not
  * yet read. */

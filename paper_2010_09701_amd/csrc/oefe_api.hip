@@ -206,7 +206,7 @@ int upload_potential_parts(oefe_op_s* op, std::string& err) {
   if ((rc = dset(op->d.fr_val, frv, err))) return rc;
   if ((rc = dset(op->d.fr_valf, to_float(frv), err))) return rc;
   {
-    std::vector<double> tv((size_t)op->tile_slots * kTileRows * E, 0.0);
+    std::vector<double> tv((size_t)tile_offset(op->tile_slots, op->n_tiles, op->tile_pad) * E, 0.0);
     for (int64_t k = 0; k < op->fr_nnz; ++k)
       for (int e = 0; e < E; ++e) tv[(size_t)op->csr_to_tile[k] * E + e] = frv[(size_t)k * E + e];
     if (!op->d.tile_val) {
@@ -338,6 +338,7 @@ int upload_operator(oefe_op_s* op, std::string& err) {
       struct Tiling {
         std::vector<int32_t> tfptr, tfns;
         std::vector<int64_t> csr_to_tile;
+        std::vector<int32_t> nfn;  // functions of each tile, without the padding
         int fpmax = 0;
       };
       auto build_tiles = [&](int mode, Tiling& T) {
@@ -365,14 +366,17 @@ int upload_operator(oefe_op_s* op, std::string& err) {
             const int g = tile_node(t, r, op->n, mode);
             if (g < 0) continue;
             for (int64_t k = fr_ptr[g]; k < fr_ptr[g + 1]; ++k)
-              T.csr_to_tile[k] = (int64_t)T.tfptr[t] * kTileRows + (int64_t)r * FP + slot[fr_fn[k]];
+              T.csr_to_tile[k] = tile_offset(T.tfptr[t], t, op->tile_pad) + (int64_t)r * (FP + op->tile_pad) + slot[fr_fn[k]];
           }
-          for (int j = 0; j < FP; ++j) T.tfns.push_back(j < F ? fl[j] : -1);
+          // the padding repeats the last function (its coupling values are zero)
+          for (int j = 0; j < FP; ++j) T.tfns.push_back(fl[std::min(j, F - 1)]);
+          T.nfn.push_back(F);
           for (int32_t f : fl) slot[f] = -1;
           T.tfptr[t + 1] = T.tfptr[t] + FP;
           T.fpmax = std::max(T.fpmax, FP);
         }
       };
+      op->tile_pad = op->poisson ? 0 : 2;
       Tiling T0, T1;
       build_tiles(0, T0);
       build_tiles(1, T1);
@@ -394,13 +398,15 @@ int upload_operator(oefe_op_s* op, std::string& err) {
       }
       // per function: its (tile, slot) partial positions, in tile order
       std::vector<int32_t> fpp(op->n_enr + 1, 0);
-      for (int32_t f : tfns)
-        if (f >= 0) fpp[f + 1]++;
+      auto each_slot = [&](auto&& f) {
+        for (int64_t t = 0; t < op->n_tiles; ++t)
+          for (int32_t q = tfptr[t]; q < tfptr[t] + T.nfn[t]; ++q) f(q, tfns[q]);
+      };
+      each_slot([&](int32_t, int32_t fn) { fpp[fn + 1]++; });
       for (int f = 0; f < op->n_enr; ++f) fpp[f + 1] += fpp[f];
       std::vector<int32_t> fpo(fpp[op->n_enr]);
       std::vector<int32_t> ff(fpp.begin(), fpp.end() - 1);
-      for (size_t q = 0; q < tfns.size(); ++q)
-        if (tfns[q] >= 0) fpo[ff[tfns[q]]++] = (int32_t)q;
+      each_slot([&](int32_t q, int32_t fn) { fpo[ff[fn]++] = q; });
       op->fn_smax = 0;
       for (int f = 0; f < op->n_enr; ++f) op->fn_smax = std::max(op->fn_smax, fpp[f + 1] - fpp[f]);
       if ((rc = dput(&op->d.tile_fptr, tfptr, err))) return rc;
@@ -648,13 +654,11 @@ int overlap_setup(const oefe_op_s* op, Overlap* ov) {
     const unsigned fl = hipEventDisableTiming | hipEventDisableSystemFence;
     hipError_t e = hipStreamCreateWithFlags(&op->side_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&op->ev_node, fl);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&op->ev_k1, fl);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&op->ev_zo, fl);
     if (e != hipSuccess) return hip_fail(e, "overlap stream setup");
   }
   ov->side = op->side_stream;
   ov->ev_node = op->ev_node;
-  ov->ev_k1 = op->ev_k1;
   ov->ev_zo = op->ev_zo;
   ov->first = ov->last = false;
   return OEFE_OK;
@@ -1136,6 +1140,7 @@ int filter_impl(oefe_op_s* op, bool bf16, T* X, int64_t ld, int nv, int m, doubl
   }
   Overlap ov;
   if (int rc = overlap_setup(op, &ov)) return rc;
+  StepWork sw = L.step;
   // on an error the main stream still waits for the side chain already queued
   auto bail = [&](int rc) {
     if (rc != OEFE_EINVAL) (void)hipStreamWaitEvent(s, ov.ev_zo, 0);
@@ -1144,8 +1149,9 @@ int filter_impl(oefe_op_s* op, bool bf16, T* X, int64_t ld, int nv, int m, doubl
   // Y_1 = (s1/e)(H x - c x)  -> old buffer
   ov.first = true;
   ov.last = m == 1;
-  int rc = apply_step<T>(op, bf16, cur, ldu, nullptr, old, ldu, nv, s1 / e, c, 0.0, L.step, s, &ov, dsc);
+  int rc = apply_step<T>(op, bf16, cur, ldu, nullptr, old, ldu, nv, s1 / e, c, 0.0, sw, s, &ov, dsc);
   if (rc) return bail(rc);
+  std::swap(sw.zo, sw.zn);
   std::swap(cur, old);  // cur = Y1, old = Y0
   double sig = s1;
   for (int k = 1; k < m; ++k) {
@@ -1153,9 +1159,10 @@ int filter_impl(oefe_op_s* op, bool bf16, T* X, int64_t ld, int nv, int m, doubl
     ov.first = false;
     ov.last = k == m - 1;
     // (device scalars: the host beta only marks that prev is read)
-    rc = apply_step<T>(op, bf16, cur, ldu, old, old, ldu, nv, 2.0 * sn / e, c, dsc ? 1.0 : sig * sn, L.step, s, &ov,
+    rc = apply_step<T>(op, bf16, cur, ldu, old, old, ldu, nv, 2.0 * sn / e, c, dsc ? 1.0 : sig * sn, sw, s, &ov,
                        dsc ? dsc + 3 * k : nullptr);
     if (rc) return bail(rc);
+    std::swap(sw.zo, sw.zn);
     std::swap(cur, old);
     sig = sn;
   }
@@ -1378,7 +1385,6 @@ int oefe_op_destroy(oefe_op op) {
     (void)hipStreamSynchronize(op->side_stream);
     (void)hipStreamDestroy(op->side_stream);
     (void)hipEventDestroy(op->ev_node);
-    (void)hipEventDestroy(op->ev_k1);
     (void)hipEventDestroy(op->ev_zo);
   }
   free_device(op);
@@ -1767,6 +1773,10 @@ int filter_batched_impl(int nk, const oefe_op* ops, bool bf16, void* const* X, c
   int rc = apply_step_batch<T>(opp, nk, bf16, xin.data(), ldp.data(), pin.data(), outp.data(), ldp.data(), nvv.data(),
                                al.data(), c.data(), be.data(), sw.data(), s, &ov);
   if (rc) return bail(rc);
+  auto next_z = [&] {
+    for (int q = 0; q < nk; ++q) std::swap(sw[q].zo, sw[q].zn);
+  };
+  next_z();
   T** cur = B.data();
   T** old = A.data();
   for (int k = 1; k < m; ++k) {
@@ -1784,6 +1794,7 @@ int filter_batched_impl(int nk, const oefe_op* ops, bool bf16, void* const* X, c
     rc = apply_step_batch<T>(opp, nk, bf16, xin.data(), ldp.data(), pin.data(), outp.data(), ldp.data(), nvv.data(),
                              al.data(), c.data(), be.data(), sw.data(), s, &ov);
     if (rc) return bail(rc);
+    next_z();
     std::swap(cur, old);
   }
   for (int q = 0; q < nk; ++q) {

@@ -80,8 +80,15 @@ __host__ __device__ inline int tile_node(int t, int r, int n, int mode) {
   tile_origin(t, n, mode, x0, y0, z0);
   return tile_row_node(x0, y0, z0, r, n, mode);
 }
-// enrichment functions one tile may couple to: the node-stage kernels stage a tile's dense
-// block (complex: two planes of kTileRows x (F + 1) float64) in 150 KB of LDS
+// Storage of a tile's dense coupling block: rows of FP + pad elements (FP: the tile's padded function
+// count, a multiple of 4).  pad = 2: the block can be copied to LDS as it is and 32 lanes reading two
+// functions of 16 rows touch distinct banks (float64: twice the stride is 4 mod 8), with rows aligned
+// to pairs.  pad = 0 for the auxiliary-potential operator, whose one-column node stage streams the
+// blocks (11 functions a tile on diamond64).  The blocks follow one another, tile t with functions from
+// list position f0 at tile_offset(f0, t, pad) elements.
+__host__ __device__ constexpr int64_t tile_offset(int64_t f0, int64_t t, int pad) { return (f0 + pad * t) * kTileRows; }
+// enrichment functions one tile may couple to: the node kernel holds a tile's dense block (complex:
+// kTileRows x (F + 2) pairs of float64) in 150 KB of LDS
 constexpr int kTileFunctionsMax = 144;
 
 using cplx = std::complex<double>;
@@ -142,8 +149,9 @@ struct DeviceArrays {
   double* fr_val = nullptr;
   float* fr_valf = nullptr;
   // tile-dense enrichment coupling: FE rows in tiles of kTileRows; tile t couples to the
-  // functions tile_fns[tile_fptr[t] .. tile_fptr[t+1]) (padded to a multiple of 4 with -1)
-  // with dense values tile_val[(tile_fptr[t] * kTileRows + r * FP_t + j)] (complex: x2),
+  // functions tile_fns[tile_fptr[t] .. tile_fptr[t+1]) (padded to a multiple of 4 by repeats of the
+  // last function with zero values)
+  // with dense values tile_val[tile_offset(tile_fptr[t], t, pad) + r * (FP_t + pad) + j] (complex: x2),
   // pre-scaled by m_g^-1/2.  Transposed partials are reduced per function over the list
   // fn_poff[fn_pptr[nu] .. fn_pptr[nu+1]) of (tile_fptr[t] + j) slots.
   int32_t* tile_fptr = nullptr;
@@ -281,6 +289,7 @@ struct oefe_op_s {
   int64_t n_tiles = 0, tile_slots = 0;        // tiles, total padded (tile, function) slots
   int tile_mode = 0;                           // coupling-tile shape (tile_count)
   int tile_fpmax = 0;
+  int tile_pad = 2;                            // padding of the rows of tile_val (tile_offset)
   int fn_smax = 0;  // most tile partials of one enrichment function
   oefe::DeviceArrays d;
   // launch shape overrides (autotuner): cell-kernel column width, node/partial column block
@@ -291,7 +300,7 @@ struct oefe_op_s {
   int timer_kind = 0;  // oefe_timer_kind
   // side stream and events of the overlapped recurrence (created on first use)
   mutable hipStream_t side_stream = nullptr;
-  mutable hipEvent_t ev_node = nullptr, ev_k1 = nullptr, ev_zo = nullptr;
+  mutable hipEvent_t ev_node = nullptr, ev_zo = nullptr;
   mutable std::vector<std::pair<hipEvent_t, hipEvent_t>> timer_events;
 };
 

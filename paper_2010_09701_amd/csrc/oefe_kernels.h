@@ -10,6 +10,7 @@ struct StepWork {
   void* ycell;    // [n_cells * nd * ldc] real columns, element T
   int ldc;        // real columns per cell node (padded)
   void* zo;       // [n_enr * ncr] S X^O
+  void* zn;       // [n_enr * ncr] the next step's (a recurrence exchanges the two after each step)
   void* part;     // [tile_slots * ncr] per-tile partials of (m^-1/2 H^co)^* X
   void* part2;    // [n_enr * n_rchunks * ncr] partials folded over chunks of tiles
   void* wp;       // [n_enr * ncr]
@@ -26,15 +27,16 @@ inline hipError_t allow_dynamic_lds(const void* kernel, size_t dynamic_bytes) {
 size_t step_work_bytes(const oefe_op_s* op, int elem_bytes, bool cplx, int nv, int* ldc_out);
 StepWork carve_step_work(const oefe_op_s* op, int elem_bytes, bool cplx, int nv, void* work);
 
-// Overlap of a recurrence: the enrichment side of step k (the coupling kernel, then
-// the partial fold, W', the enrichment rows of out and Z^O of step k+1) runs on `side`
-// beside the cell stage of step k; the node assembly of step k waits for the coupling
-// kernel (ev_k1), and the side work of step k+1 waits for that assembly (ev_node).
-// first: this step computes its own Z^O; last: the main stream waits for the side
-// chain (ev_zo) at the end of the step.
+// Overlap of a recurrence: the enrichment side of step k (W' and the enrichment rows of out from the
+// folded partials, Z^O of step k+1 into the buffer that step k's node stage does not read) runs on
+// `side` beside step k's cell and node stages; then, after the node stage (ev_node), which formed step
+// k+1's partials from its result, their fold beside the cell stage of step k+1, whose node stage waits
+// for it (ev_zo).
+// first: this step computes its own Z^O and partials; last: the main stream waits for the side
+// chain at the end of the step.
 struct Overlap {
   hipStream_t side;
-  hipEvent_t ev_node, ev_k1, ev_zo;
+  hipEvent_t ev_node, ev_zo;
   bool first, last;
 };
 

@@ -4,12 +4,13 @@
 // One operator step (out = alpha (Ht x - c x) - beta prev) is:
 //   1. zo       Z^O = S X^O                                   (small dense)
 //   2. cell     per cell: z_e = m^-1/2 (theta o X)|_e, y_e = K_e z_e + B^T diag(W V) B z_e
-//               (sum-factorized, see fe_cell_kernel) -> per-cell buffer
-//   3. partial  per 64-row tile: conj(m^-1/2 H^co)^T X over the tile's rows
-//   4. node     per FE node: fixed-order sum of the (up to 8) cell results sharing it
-//               (no atomics), times m^-1/2, + (m^-1/2 H^co) Z^O, recurrence epilogue
-//   5. reduce   W' = sum of the tile partials of each function (fixed order)
-//   6. gemm     W' += H^oo Z^O ;  enrichment rows alpha (S W' - c x) - beta prev
+//               (sum-factorized, see fe_cell_kernel) -> node-slot grid
+//   3. node     per FE node: fixed-order sum of the (up to 8) cell results sharing it
+//               (no atomics), times m^-1/2, + (m^-1/2 H^co) Z^O, recurrence epilogue; per 64-row
+//               tile the partial conj(m^-1/2 H^co)^T X over its rows (in a recurrence, of the X
+//               that this step writes)
+//   4. reduce   W' = sum of the tile partials of each function (fixed order)
+//   5. gemm     W' += H^oo Z^O ;  enrichment rows alpha (S W' - c x) - beta prev
 // Every launch can cover several operators of one mesh at once (k-points): the
 // per-operator arguments travel in a KBatch and blockIdx.z selects the operator.
 #include <hip/hip_runtime.h>
@@ -53,7 +54,8 @@ struct KP {
   int nv, ncr;  // vectors (complex elements when complex) and real columns
   T* ycell;
   int ldc;
-  T* zo;
+  T* zo;  // Z^O of this step
+  T* zn;  // Z^O of the next one (a recurrence)
   T* part;
   T* part2;
   int nch;  // chunks per function in part2
@@ -985,25 +987,28 @@ __global__ __launch_bounds__(768) void fe_cell_bf16_kernel(KBatch<float> kb, con
 }
 
 // ---------------------------------------------------------------------------
-// Node stage, split in two kernels so that the dense coupling work leaves the
-// critical path:
+// Node stage: out = alpha (m^-1/2 sum_slots(Y) + Ht_t Z^O - c x) - beta prev on the FE rows, and the
+// tile's partial part_t = Ht_t^* X_t of the enrichment rows' H^co* X (Ht_t: the tile's dense block of
+// m^-1/2 H^co).
 //
-// fe_coupling_kernel (side stream, beside the cell stage; needs only X and Z^O):
-//   for each coupling tile t of kTileRows FE rows (tile_node) and each group of 16 NBW real columns
-//     part_t = Ht_t^* X_t              -> per-tile partial of W' (reduced later)
-//     out_t  = alpha Ht_t Z^O - beta prev_t
-//   (Ht_t: the tile's dense block of m^-1/2 H^co) on the matrix cores (16x16x4 MFMA,
-//   float64 or float32).  One wave per (tile, column group), no LDS and no barriers: the
-//   tile's block and Z^O are read through the caches, shared by the waves of a tile.
+// One wave per (half a coupling tile of kTileRows rows, column group of 16 NC real columns); the waves
+// of up to 4 column groups share the tile's coupling block in LDS, copied there without passing
+// through registers, and a table of what each row needs (offsets, factors, flags).  A wave holds its
+// rows in the layout of the 16x16x4 MFMA result (row 16 rb + M::row(lane, v), column lane % 16), so that
+// Ht_t Z^O, slot sums, X, previous iterate and output meet in registers without a transpose; all its
+// loads are issued before the first is used.  In a recurrence the partial is formed from the result,
+// which is the next step's X: only there are rows exchanged (LDS tile of the column group), each half
+// taking alternate blocks of 16 functions.
 //
-// fe_assemble_kernel (main stream, after the cell stage), one element per thread:
-//   out = alpha (m^-1/2 sum_slots(Y) - c x) + base,  base = out (the coupling kernel's
-//   result) or -beta prev when the operator has no enrichment.
-//   sum_slots adds, in a fixed order, the (up to 8) cell results stored for the node in
-//   the node-slot grid (no atomics).
+// What bounds it: memory latency against waves in flight.  At 128 registers 16 waves are resident on a
+// CU (a kernel of 16 rows x 64 columns per wave, X and Z^O through LDS: 8).  diamond64, 320 columns:
+// float64 3750 -> 3030 us (13.6 GB, 4.5 TB/s of the copy kernel's 5.5), float32 1870 -> 1470 us; diamond8,
+// 72 columns: 110 -> 100 us and 54 -> 60 us (17 thousand waves: 4.2 rounds of the device); Bloch operators,
+// four k-points of 67..96 complex128 columns: 1000 us beside the cell stage + 600 us in two kernels ->
+// 1050 us in one (a degree 2000 -> 1690 us).
 //
-// Complex columns are interleaved (re, im); a complex product is two real MFMA passes
-// over the real and imaginary parts of Ht with the matching (swapped, signed) columns.
+// Complex columns are interleaved (re, im); a complex product is two real MFMA passes over the real
+// and imaginary parts of Ht with the matching (swapped, signed) columns.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Mfma;
@@ -1025,719 +1030,543 @@ struct Mfma<float> {
   static __device__ __forceinline__ int row(int l, int v) { return 4 * (l >> 4) + v; }
 };
 
-constexpr int kCoupleNBWMax = 2;  // 16-column blocks per coupling wave
+// a / p for the supported element degrees p = 2, 3, 4 (a >= 0): constant divisors
+__device__ __forceinline__ int div_p(int a, int p) { return p == 4 ? a >> 2 : (p == 2 ? a >> 1 : a / 3); }
 
-// LDS of the coupling kernel: the tile's block, one plane per real / imaginary part, rows
-// of FP + 1 (odd) elements so that 16 lanes reading 16 consecutive functions of a row, or
-// one function of 16 consecutive rows, touch 16 distinct bank pairs; then the function list.
-__host__ __device__ constexpr int coupling_row_stride(int fp) { return fp + 1; }
+constexpr int kNodeGroups = 4;  // column groups of a node workgroup at most: two waves each
 
+// NC consecutive columns of a row, loaded or stored together (rows need not be aligned to pairs)
+template <typename T, int NC>
+struct ColVec {
+  T e[NC];
+};
+template <typename T, int NC>
+__device__ __forceinline__ ColVec<T, NC> load_cols(const T* p) {
+  ColVec<T, NC> r;
+  __builtin_memcpy(&r, p, sizeof(r));
+  return r;
+}
+
+// LDS of a node workgroup whose waves work on up to ntl consecutive tiles: their coupling blocks as
+// they are stored (one after the other, see tile_offset), in whole 1 KB pieces (one 16-byte element
+// per lane) and with 16 functions to spare, read past the last row and unused; then their lists.
 template <typename T, bool CPLX>
-constexpr size_t coupling_lds_bytes(int fpmax) {
-  return (size_t)(CPLX ? 2 : 1) * kTileRows * coupling_row_stride(fpmax) * sizeof(T) + (size_t)fpmax * sizeof(int32_t);
+__host__ __device__ constexpr size_t node_block_bytes(int fpmax, int pad, int ntl) {
+  return ((size_t)(kTileRows * (fpmax + pad) * ntl + 16) * (CPLX ? 2 : 1) * sizeof(T) + 1023) / 1024 * 1024;
+}
+__host__ __device__ constexpr size_t node_list_bytes(int fpmax, int ntl) {
+  return ((size_t)ntl * fpmax + 63) / 64 * 64 * sizeof(int32_t);  // 64 entries (one per lane) at a time
+}
+// What the node stage needs of each tile row, formed once per workgroup: the FE row, element offset of its
+// first slot in the node-slot grid, m^-1/2, the step to the next slot where the node is shared in x
+// (else 0), flags (shared in y, z: a second slot there; first slot a periodic image in x, y, z; in
+// the mesh).  Rows past the mesh: those of row 0, no flags.
+template <typename T>
+struct alignas(8) NodeRow {
+  int64_t slot;
+  T msc;
+  int32_t row, dx, flags;
+};
+enum { kY2 = 1, kZ2 = 2, kXW = 4, kYW = 8, kZW = 16, kIn = 32 };
+// Work space of a node workgroup: the blocks, the rows of its tiles, their lists, and a
+// kTileRows x (16 NC) tile of values per column group
+struct NodeLds {
+  size_t rows, lists, x, total;
+};
+template <typename T, bool CPLX, int NC>
+__host__ __device__ constexpr NodeLds node_lds(int fpmax, int pad, int ntl, int groups) {
+  NodeLds l{};
+  l.rows = fpmax > 0 ? node_block_bytes<T, CPLX>(fpmax, pad, ntl) : 0;
+  l.lists = l.rows + (size_t)ntl * kTileRows * sizeof(NodeRow<T>);
+  l.x = l.lists + node_list_bytes(fpmax, ntl);
+  l.total = l.x + (fpmax > 0 ? (size_t)groups * kTileRows * 16 * NC * sizeof(T) : 0);
+  return l;
+}
+// tiles that w consecutive (tile, column group) items touch, the first at a multiple of w, gp
+// groups per tile
+__host__ __device__ constexpr int node_tiles(int gp, int w) {
+  return gp % w == 0 ? 1 : (w % gp == 0 ? w / gp : (w - 1 + gp - 1) / gp + 1);
 }
 
-// part columns of NQ blocks of 16 functions (from function m0) over the tile's TR rows:
-// pc[q][nb] += Ht_t[r][m0 + 16 q + .]^* x[r][cols of block nb], k-steps of 4 rows with the
-// x loads of 4 k-steps issued ahead of their MFMAs; Ht_t from LDS (planes hs[e])
-template <typename T, int NQ, int NBW, bool CPLX>
-__device__ __forceinline__ void coupling_part(const T* hs, int HS, const T* __restrict__ x, int64_t ldx, int tx0,
-                                              int ty0, int tz0, int n, int tm, int FP, int m0, const int (&colc)[NBW], int li,
-                                              int lk,
-                                              typename Mfma<T>::V4 (&pc)[4][NBW]) {
-  using M = Mfma<T>;
-  constexpr int TR = kTileRows, E = CPLX ? 2 : 1, KB = 4;
-  const T sgn = (li & 1) ? T(-1) : T(1);
-  int fcl[NQ];
-  bool fok[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int f = m0 + q * 16 + li;
-    fok[q] = f < FP;
-    fcl[q] = fok[q] ? f : FP - 1;
-  }
-  for (int ks0 = 0; ks0 < TR / 4; ks0 += KB) {
-    T b[KB][E][NBW];
-#pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int r = (ks0 + j) * 4 + lk;
-      const int gt = tile_row_node(tx0, ty0, tz0, r, n, tm);
-      const bool rok = gt >= 0;
-      const int64_t g = rok ? gt : 0;
-#pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) {
-        // multiply by 1 or 0 rather than select: keeps the load unconditional and batched
-        b[j][0][nb] = x[g * ldx + colc[nb]] * (rok ? T(1) : T(0));
-      }
+// A wave's share of the node stage: half the rows of a tile (two groups of 16) x a column group, and the
+// tile's coupling block and list in LDS.
+struct NodeItem {
+  int t, dt, cb0, f0, FP;  // tile, and its place among the workgroup's
+  size_t blk;  // byte offset of the tile's block in LDS
+  int list;    // first entry of its list
+  int half, grp;  // which half of the tile; column group of the workgroup
+  bool live;   // else the wave only helps with the copies
+};
+
+// The mesh of a node or part kernel launch
+struct NodeMesh {
+  int nc, p, n, P1, N, tm, ntiles;
+  int fpmax, pad, ntl, span;
+};
+
+// span: a workgroup's waves take consecutive (tile, column group) items across tile ends; else each
+// tile's groups are padded to whole workgroups.  Launch order: the column groups of a tile are
+// consecutive, and each XCD (workgroups bk = x mod 8) takes a contiguous range, so the groups that
+// read the same coupling block, and neighbouring tiles, share one L2.  Starts the copies of the blocks
+// and lists and forms the rows (cf not null); both are to be followed by a barrier.  Returns false (the
+// whole workgroup) past the operator's items.
+template <typename T, bool CPLX, int NC>
+__device__ __forceinline__ bool node_item(const KP<T>& P, const NodeMesh& g, const int32_t* __restrict__ tile_fptr,
+                                          const int32_t* __restrict__ tile_fns, const CellCoef<T>* cf,
+                                          unsigned char* smem, const NodeLds& lds, NodeItem& it) {
+  constexpr int E = CPLX ? 2 : 1;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), nw = (int)(blockDim.x >> 6), W = nw >> 1;
+  it.half = w & 1;
+  it.grp = w >> 1;
+  const int G = (P.ncr + 16 * NC - 1) / (16 * NC), GP = g.span ? G : (G + W - 1) / W * W;  // groups of a tile
+  const int items = g.ntiles * GP, nbk = (items + W - 1) / W, bk = blockIdx.x, nb8 = nbk & ~7;
+  if (bk >= nbk) return false;
+  const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
+  const int item = min(L * W + it.grp, items - 1);
+  const int t0 = L * W / GP, t1 = min(L * W + W - 1, items - 1) / GP;  // the workgroup's tiles
+  it.t = item / GP;
+  it.dt = it.t - t0;
+  it.cb0 = (item - it.t * GP) * 16 * NC;
+  it.live = L * W + it.grp < items && it.cb0 < P.ncr;
+  if (!it.live) it.cb0 = 0;  // its loads stay in bounds, it stores nothing
+  it.f0 = it.FP = it.list = 0;
+  it.blk = 0;
+  if (tile_fptr) {
+    const int fa = tile_fptr[t0], fb = tile_fptr[t1 + 1];
+    it.f0 = tile_fptr[it.t];
+    it.FP = tile_fptr[it.t + 1] - it.f0;
+    it.list = it.f0 - fa;
+    it.blk = (size_t)(tile_offset(it.f0, it.t, g.pad) - tile_offset(fa, t0, g.pad)) * E * sizeof(T);
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(P.tv + tile_offset(fa, t0, g.pad) * E);
+    const unsigned nbytes = (unsigned)((tile_offset(fb, t1 + 1, g.pad) - tile_offset(fa, t0, g.pad)) * E * sizeof(T));  // 256 m
+    for (unsigned q = (unsigned)w * 1024u; q < nbytes; q += (unsigned)nw * 1024u) {
+      const unsigned o = min(q + (unsigned)lane * 16u, nbytes - 16u);  // the last piece: in bounds, not used
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + o),
+                                       (__attribute__((address_space(3))) void*)(smem + q), 16, 0, 0);
     }
-#pragma unroll
-    for (int j = 0; j < KB; ++j) {
-      const int r = (ks0 + j) * 4 + lk;
-      if constexpr (CPLX) {
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) b[j][1][nb] = sgn * __shfl_xor(b[j][0][nb], 1);
-      }
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const T av = hs[(e * TR + r) * HS + fcl[q]];
-          const T a = fok[q] ? av : T(0);
-#pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) pc[q][nb] = M::op(a, b[j][e][nb], pc[q][nb]);
-        }
+    for (int q = w * 64; q < fb - fa; q += nw * 64)  // the lists, 64 entries a wave
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(tile_fns + min(fa + q + lane, fb - 1)),
+          (__attribute__((address_space(3))) void*)(smem + lds.lists + (size_t)q * sizeof(int32_t)), 4, 0, 0);
+  }
+  if (cf) {
+    NodeRow<T>* rows = reinterpret_cast<NodeRow<T>*>(smem + lds.rows);
+    const int S = g.nc * g.P1;
+    for (int q = threadIdx.x; q < (t1 - t0 + 1) * kTileRows; q += blockDim.x) {
+      int x0, y0, z0, ix, iy, iz;
+      tile_origin(t0 + q / kTileRows, g.n, g.tm, x0, y0, z0);
+      const bool in = tile_row_coords(x0, y0, z0, q % kTileRows, g.n, g.tm, ix, iy, iz) >= 0;
+      // slots of node i per dimension: a shared node (i mod p == 0) has two, the one from the lower
+      // cell first; slot 0 holds the periodic image of the last cell
+      const int qx = div_p(ix, g.p), rx = ix - qx * g.p, qy = div_p(iy, g.p), ry = iy - qy * g.p,
+                qz = div_p(iz, g.p), rz = iz - qz * g.p;
+      const int bx = qx * g.P1 + (rx ? rx + 1 : 0), by = qy * g.P1 + (ry ? ry + 1 : 0),
+                bz = qz * g.P1 + (rz ? rz + 1 : 0);
+      NodeRow<T> r;
+      r.row = in ? ix + g.n * (iy + g.n * iz) : 0;
+      r.slot = in ? (int64_t)(bx + S * (by + S * bz)) * P.ldc : 0;
+      r.msc = cf->mscale * cf->om[rx] * cf->om[ry] * cf->om[rz];
+      r.dx = in && rx == 0 ? P.ldc : 0;
+      r.flags = in ? kIn | (ry == 0 ? kY2 : 0) | (rz == 0 ? kZ2 : 0) | (bx == 0 ? kXW : 0) | (by == 0 ? kYW : 0) |
+                         (bz == 0 ? kZW : 0)
+                   : 0;
+      rows[q] = r;
     }
   }
+  return true;
 }
 
-template <typename T, int NBW, bool CPLX>
-__global__ __launch_bounds__(256, NBW == 1 ? 2 : 1) void fe_coupling_kernel(KBatch<T> kb, const int32_t* __restrict__ tile_fptr,
-                                                          const int32_t* __restrict__ tile_fns, int n, int tm) {
+// Barrier of the workgroup for LDS written by its waves; loads from memory stay under way
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// Barrier for the blocks and lists copied by node_item: a wave's copies were issued before the load of v
+// and loads complete in order, so they are in LDS once v is here
+template <typename V>
+__device__ __forceinline__ void copied_barrier(V v) {
+  asm volatile("" ::"v"(v));
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// part_t[f][columns] = Ht_t^* X_t, in two parts: the two waves of a column group put their rows of X_t
+// (x[rb][v], in the layout of the MFMA result; 0 past the mesh) into the group's LDS tile, then, after a
+// barrier of the whole workgroup, take alternate blocks of 16 functions over all rows (functions past
+// the list give rows that are not stored).
+template <typename T, int NC>
+__device__ __forceinline__ void node_stash(T* xt, const NodeItem& it, const ColVec<T, NC> (&x)[2][4]) {
+  const int lane = threadIdx.x & 63;
+  ColVec<T, NC>* xs = reinterpret_cast<ColVec<T, NC>*>(xt) + it.grp * kTileRows * 16;  // [kTileRows][16]
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      xs[(it.half * 32 + rb * 16 + Mfma<T>::row(lane, v)) * 16 + (lane & 15)] = x[rb][v];
+}
+template <typename T, bool CPLX, int NC>
+__device__ __forceinline__ void node_part(const KP<T>& P, const T* hs, int HS, const T* xt, const NodeItem& it) {
   using M = Mfma<T>;
   using V4 = typename M::V4;
-  constexpr int TR = kTileRows, E = CPLX ? 2 : 1, RB = TR / 16, HPT = 8;
+  using CV = ColVec<T, NC>;
+  constexpr int E = CPLX ? 2 : 1;
+  const int lane = threadIdx.x & 63, li = lane & 15, FP = it.FP, ncr = P.ncr;
+  const int col = it.cb0 + NC * li;
+  const CV* xs = reinterpret_cast<const CV*>(xt) + it.grp * kTileRows * 16;
+  lds_barrier();
+  if (!it.live) return;
+  const T sp = (li & 1) ? T(-1) : T(1);  // NC = 1: sign of the partner's part
+  for (int m0 = 16 * it.half; m0 < FP; m0 += 32) {
+    V4 pc[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) pc[j] = V4{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < kTileRows / 4; ++ks) {
+      const int r = 4 * ks + (lane >> 4);
+      const T* h = hs + (unsigned)(r * HS + m0 + li) * E;
+      const CV xv = xs[r * 16 + li];
+      if constexpr (CPLX) {
+        const T hr = h[0], hi = h[1];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) pc[j] = M::op(hr, xv.e[j], pc[j]);
+        if constexpr (NC == 2) {
+          pc[0] = M::op(hi, xv.e[1], pc[0]);
+          pc[1] = M::op(-hi, xv.e[0], pc[1]);
+        } else {
+          pc[0] = M::op(hi, sp * __shfl_xor(xv.e[0], 1), pc[0]);
+        }
+      } else {
+        const T hv = h[0];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) pc[j] = M::op(hv, xv.e[j], pc[j]);
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int f = m0 + M::row(lane, v);
+      T* o = P.part + (int64_t)(it.f0 + f) * ncr + col;
+      if (f < FP) {
+        if (NC == 2 && col + 1 < ncr) {
+          const ColVec<T, 2> q{{pc[0][v], pc[NC - 1][v]}};
+          __builtin_memcpy(o, &q, sizeof(q));
+        } else if (col < ncr) {
+          o[0] = pc[0][v];
+        }
+      }
+    }
+  }
+}
+
+// X of a wave's columns: from clamped columns (loads stay in bounds; the values of columns past ncr
+// are not used).  NC = 2 needs ncr >= 2; an odd last column sits in the second element of the pair
+// that ends there.
+template <typename T, int NC>
+__device__ __forceinline__ ColVec<T, NC> load_row(const T* row, int col, int ncr) {
+  ColVec<T, NC> r = load_cols<T, NC>(row + min(col, ncr - NC));
+  if constexpr (NC == 2) {
+    if (ncr & 1) r.e[0] = col == ncr - 1 ? r.e[1] : r.e[0];
+  }
+  return r;
+}
+
+// part of a block's first step (later steps form it from their result): fe_part_kernel, same tiles
+// and column groups as the node kernel
+template <typename T, bool CPLX, int NC>
+__global__ __launch_bounds__(128 * kNodeGroups, 4) void fe_part_kernel(KBatch<T> kb, NodeMesh g,
+                                                                       const int32_t* __restrict__ tile_fptr,
+                                                                       const int32_t* __restrict__ tile_fns) {
+  using M = Mfma<T>;
+  extern __shared__ unsigned char smem_raw[];
+  const KP<T>& P = kb.k[blockIdx.z];
+  const NodeLds lds = node_lds<T, CPLX, NC>(g.fpmax, g.pad, g.ntl, (int)(blockDim.x >> 7));
+  NodeItem it;
+  if (!node_item<T, CPLX, NC>(P, g, tile_fptr, tile_fns, nullptr, smem_raw, lds, it)) return;
+  const int lane = threadIdx.x & 63, col = it.cb0 + NC * (lane & 15);
+  int tx0, ty0, tz0;
+  tile_origin(it.t, g.n, g.tm, tx0, ty0, tz0);
+  ColVec<T, NC> x[2][4];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int gr = tile_row_node(tx0, ty0, tz0, it.half * 32 + rb * 16 + M::row(lane, v), g.n, g.tm);
+      x[rb][v] = load_row<T, NC>(P.x + (int64_t)max(gr, 0) * P.ldx, col, P.ncr);
+#pragma unroll
+      for (int j = 0; j < NC; ++j) x[rb][v].e[j] = gr >= 0 ? x[rb][v].e[j] : T(0);
+    }
+  copied_barrier(x[1][3].e[0]);
+  T* xt = reinterpret_cast<T*>(smem_raw + lds.x);
+  node_stash<T, NC>(xt, it, x);
+  node_part<T, CPLX, NC>(P, reinterpret_cast<const T*>(smem_raw + it.blk), it.FP + g.pad, xt, it);
+}
+
+// PX: part of this step's X (a single application); else part of the step's result, which is the next
+// step's X, when pnext.
+template <typename T, bool CPLX, int NC, bool PX>
+__global__ __launch_bounds__(128 * kNodeGroups, 4) void fe_node_kernel(KBatch<T> kb, NodeMesh g, CellCoef<T> cf,
+                                                                       const int32_t* __restrict__ tile_fptr,
+                                                                       const int32_t* __restrict__ tile_fns, int pnext) {
+  using M = Mfma<T>;
+  using V4 = typename M::V4;
+  using CV = ColVec<T, NC>;
+  constexpr int E = CPLX ? 2 : 1, RB = 2;  // groups of 16 rows of a wave
   extern __shared__ unsigned char smem_raw[];
   const KP<T>& P = kb.k[blockIdx.z];
   const int ncr = P.ncr;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
-  const int t = blockIdx.x;
-  int tx0, ty0, tz0;
-  tile_origin(t, n, tm, tx0, ty0, tz0);
-  const int f0 = tile_fptr[t], FP = tile_fptr[t + 1] - f0;  // FP: a multiple of 4
-  const int HS = coupling_row_stride(FP);
-  T* hs = reinterpret_cast<T*>(smem_raw);                   // [E][TR][HS]
-  int32_t* fs = reinterpret_cast<int32_t*>(hs + E * TR * HS);  // [FP]
-  const T* __restrict__ tv = P.tv + (int64_t)f0 * TR * E;   // [TR][FP][E], zero rows past the mesh
-  const T* __restrict__ x = P.x;
-  const T* __restrict__ zo = P.zo;  // [n_enr][ncr]
-  const int64_t ldx = P.ldx, ldo = P.ldo;
-  const int ngrp = (ncr + 16 * NBW - 1) / (16 * NBW);
+  const NodeLds lds = node_lds<T, CPLX, NC>(g.fpmax, g.pad, g.ntl, (int)(blockDim.x >> 7));
+  NodeItem it;
+  if (!node_item<T, CPLX, NC>(P, g, tile_fptr, tile_fns, &cf, smem_raw, lds, it)) return;
+  const int FP = it.FP, rb0 = 2 * it.half;  // the wave's rows: groups rb0, rb0 + 1 of the tile
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int col = it.cb0 + NC * li;
+  const T* hs = reinterpret_cast<const T*>(smem_raw + it.blk);  // [kTileRows][HS][E]
+  const int32_t* fs = reinterpret_cast<const int32_t*>(smem_raw + lds.lists) + it.list;
+  const NodeRow<T>* rows = reinterpret_cast<const NodeRow<T>*>(smem_raw + lds.rows) + it.dt * kTileRows + rb0 * 16;
+  T* xt = reinterpret_cast<T*>(smem_raw + lds.x);
+  const int HS = FP + g.pad;
+  T alpha, c, beta;
+  step_scalars(P, alpha, c, beta);
 
-  // ---- stage the tile's block (batches of HPT coalesced loads per thread) and its function list
-  const int nh = TR * FP * E;
-  for (int q0 = 0; q0 < nh; q0 += 256 * HPT) {
-    T hv[HPT];
+  const int colx = min(col, ncr - NC);  // columns of the loads of X, Z^O and prev (see load_row)
+  auto fix_odd = [&](CV& r) {
+    if constexpr (NC == 2) {
+      if (ncr & 1) r.e[0] = col == ncr - 1 ? r.e[1] : r.e[0];
+    }
+  };
+  lds_barrier();  // the rows
+
+  // ---- loads of all the wave's rows in one batch (element v of group rb: row 16 rb + M::row(lane, v)):
+  // X; the first slot pair of every node, its lower-x slot and, where it is shared in x, the next one
+  // (else the first again: in bounds, cached, discarded); the previous iterate (read before any element
+  // of out, which may be the same array, is written).  Slot columns past ncr (ldc >= ncr) read the next
+  // row or the grid's padding (slot_grid_elems)
+  auto row = [&](int rb, int v) -> const NodeRow<T>& { return rows[rb * 16 + M::row(lane, v)]; };
+  const T* __restrict__ Xc = P.x + colx;
+  const T* __restrict__ Y = P.ycell + col;
+  CV xr[RB][4], sa[RB][4], sb[RB][4], pv[RB][4];
 #pragma unroll
-    for (int i = 0; i < HPT; ++i) hv[i] = tv[min(q0 + (int)threadIdx.x + 256 * i, nh - 1)];
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int i = 0; i < HPT; ++i) {
-      const int q = q0 + threadIdx.x + 256 * i;
-      if (q < nh) {
-        const int r = q / (FP * E), rem = q - r * FP * E, f = rem / E, e = rem - f * E;
-        hs[(e * TR + r) * HS + f] = hv[i];
+    for (int v = 0; v < 4; ++v) xr[rb][v] = load_cols<T, NC>(Xc + row(rb, v).row * P.ldx);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const T* ya = Y + row(rb, v).slot;
+      sa[rb][v] = load_cols<T, NC>(ya);
+      sb[rb][v] = load_cols<T, NC>(ya + row(rb, v).dx);
+    }
+  const bool use_prev = beta != T(0);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (use_prev) {
+        pv[rb][v] = load_cols<T, NC>(P.prev + colx + row(rb, v).row * P.ldo);
+      } else {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) pv[rb][v].e[j] = T(0);
       }
     }
-  }
-  for (int f = threadIdx.x; f < FP; f += 256) fs[f] = tile_fns[f0 + f];
-  __syncthreads();
+  if (tile_fptr) copied_barrier(xr[RB - 1][3].e[0]);
 
-  // ---- each wave: column groups w, w + 4, ...
-  for (int grp = w; grp < ngrp; grp += 4) {
-    const int cb0 = grp * 16 * NBW;
-    // Loads are unconditional, from clamped in-bounds addresses, with unwanted values
-    // replaced by selects, so that each batch is issued at once.
-    int colc[NBW];
-    bool colok[NBW];
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb) {
-      const int col = cb0 + nb * 16 + li;
-      colok[nb] = col < ncr;
-      colc[nb] = colok[nb] ? col : ncr - 1;
-    }
-
-    // part = Ht_t^* X_t, up to 4 blocks of 16 functions at a time
-    // (complex: e = 1 pairs Im(H) with the partner column, signed)
-    for (int m0 = 0; m0 < FP; m0 += 64) {
-      V4 pc[4][NBW];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) pc[q][nb] = V4{0, 0, 0, 0};
-      const int nq = min(4, (FP - m0 + 15) / 16);
-      switch (nq) {
-        case 4: coupling_part<T, 4, NBW, CPLX>(hs, HS, x, ldx, tx0, ty0, tz0, n, tm, FP, m0, colc, li, lk, pc); break;
-        case 3: coupling_part<T, 3, NBW, CPLX>(hs, HS, x, ldx, tx0, ty0, tz0, n, tm, FP, m0, colc, li, lk, pc); break;
-        case 2: coupling_part<T, 2, NBW, CPLX>(hs, HS, x, ldx, tx0, ty0, tz0, n, tm, FP, m0, colc, li, lk, pc); break;
-        default: coupling_part<T, 1, NBW, CPLX>(hs, HS, x, ldx, tx0, ty0, tz0, n, tm, FP, m0, colc, li, lk, pc); break;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (q >= nq) break;
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-          if (!colok[nb]) continue;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int fi = m0 + q * 16 + M::row(lane, v);
-            if (fi < FP) P.part[(int64_t)(f0 + fi) * ncr + colc[nb]] = pc[q][nb][v];
-          }
-        }
-      }
-    }
-
-    // en = Ht_t Z^O for the RB 16-row blocks of the tile, k-steps of 4 functions with the
-    // Z^O loads of KB k-steps issued ahead (a k-step past the list multiplies zero columns)
-    V4 acc[RB][NBW];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) acc[rb][nb] = V4{0, 0, 0, 0};
-    {
-      constexpr int KB = 4;
-      const T sgn = (li & 1) ? T(1) : T(-1);
-      for (int k0 = 0; k0 < FP; k0 += 4 * KB) {
-        T b[KB][E][NBW];
-#pragma unroll
-        for (int j = 0; j < KB; ++j) {
-          const int f = k0 + 4 * j + lk;
-          const int fn = f < FP ? fs[f] : -1;
-          const T* __restrict__ zr = zo + (int64_t)max(fn, 0) * ncr;
-#pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) b[j][0][nb] = zr[colc[nb]] * (fn >= 0 ? T(1) : T(0));
+  // ---- node-slot sums: the lower-x slot a and (shared x node) the next one b of (ky, kz) pair kk, masks
+  // as factors (the gathered values are finite)
+  auto pair_sum = [&](int f, int dx, int kk, CV a, CV b) {
+    const T m2 = dx ? T(1) : T(0);
+    if constexpr (CPLX) {
+      // periodic images (slot 0 of a dimension came from the last cell): times the conjugate phase
+      // (NC = 1: the partner lane holds the other part of the same element)
+      auto rot = [&](CV& u, int d, bool on) {
+        CV q;
+        if constexpr (NC == 2) {
+          q.e[0] = P.ph.re[d] * u.e[0] + P.ph.im[d] * u.e[1];
+          q.e[1] = P.ph.re[d] * u.e[1] - P.ph.im[d] * u.e[0];
+        } else {
+          q.e[0] = P.ph.re[d] * u.e[0] + ((li & 1) ? -P.ph.im[d] : P.ph.im[d]) * __shfl_xor(u.e[0], 1);
         }
 #pragma unroll
-        for (int j = 0; j < KB; ++j) {
-          const int f = min(k0 + 4 * j + lk, FP - 1);
-          if constexpr (CPLX) {
+        for (int j = 0; j < NC; ++j) u.e[j] = on ? q.e[j] : u.e[j];
+      };
+      if (__any(f & kXW)) rot(a, 0, (f & kXW) != 0);
 #pragma unroll
-            for (int nb = 0; nb < NBW; ++nb) b[j][1][nb] = sgn * __shfl_xor(b[j][0][nb], 1);
-          }
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-              const T a = hs[(e * TR + rb * 16 + li) * HS + f];
-#pragma unroll
-              for (int nb = 0; nb < NBW; ++nb) acc[rb][nb] = M::op(a, b[j][e][nb], acc[rb][nb]);
-            }
-        }
-      }
-    }
-
-    // out = alpha en - beta prev (prev may be the same array as out: all of this lane's
-    // elements are read before any is written)
-    T alpha, cst, beta;
-    step_scalars(P, alpha, cst, beta);
-    T pv[RB][4][NBW];
-    if (beta != T(0)) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int64_t g = max(tile_row_node(tx0, ty0, tz0, rb * 16 + M::row(lane, v), n, tm), 0);
-#pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) pv[rb][v][nb] = beta * P.prev[g * ldo + colc[nb]];
-        }
+      for (int j = 0; j < NC; ++j) a.e[j] = fma(b.e[j], m2, a.e[j]);
+      if ((kk & 1) == 0 && __any(f & kYW)) rot(a, 1, (f & kYW) != 0);
+      if ((kk >> 1) == 0 && __any(f & kZW)) rot(a, 2, (f & kZW) != 0);
     } else {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) a.e[j] = fma(b.e[j], m2, a.e[j]);
+    }
+    return a;
+  };
+  V4 acc[RB][NC];
+  int fall = 0;    // flags of all the wave's rows
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int f = row(rb, v).flags;
+      fall |= f;
+      fix_odd(xr[rb][v]);
+      sa[rb][v] = pair_sum(f, row(rb, v).dx, 0, sa[rb][v], sb[rb][v]);
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        asm volatile("" : "+v"(sa[rb][v].e[j]));  // formed here: frees the registers of the second slots
+      }
+    }
+  if constexpr (PX) {
+    if (tile_fptr) {
+      CV xz[RB][4];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
 #pragma unroll
-          for (int nb = 0; nb < NBW; ++nb) pv[rb][v][nb] = T(0);
+          for (int j = 0; j < NC; ++j) xz[rb][v].e[j] = (row(rb, v).flags & kIn) ? xr[rb][v].e[j] : T(0);
+      node_stash<T, NC>(xt, it, xz);
     }
+  }
+
+  // ---- the slot pairs of nodes shared in y or z, in a fixed order; a pair is visited when some lane
+  // of the wave needs it, lanes that do not reload their first slot (in bounds, cached) and discard it
+  auto kflags = [](int kk) { return (kk & 1 ? kY2 : 0) | (kk & 2 ? kZ2 : 0); };
+  auto need = [&](int rb, int kk) {
+    int anyl = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) anyl |= (row(rb, v).flags & kflags(kk)) == kflags(kk);
+    return (bool)__any(anyl);
+  };
+  auto pair_load = [&](int kk, CV (&a)[RB][4], CV (&b)[RB][4]) {
+    const int S = g.nc * g.P1;
+    const int64_t kofs = (int64_t)((kk & 1 ? S : 0) + (kk & 2 ? S * S : 0)) * P.ldc;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
+      if (need(rb, kk)) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int gv = tile_row_node(tx0, ty0, tz0, rb * 16 + M::row(lane, v), n, tm);
-        if (gv < 0) continue;
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb)
-          if (colok[nb]) P.out[(int64_t)gv * ldo + colc[nb]] = alpha * acc[rb][nb][v] - pv[rb][v][nb];
-      }
-  }
-}
-
-// Flat element index -> (row, column) for rows of nel elements, without a 64-bit
-// integer division: a float64 quotient corrected by one step.
-__device__ __forceinline__ int64_t row_of(int64_t i, int nel, double rnel) {
-  int64_t g = (int64_t)((double)i * rnel);
-  const int64_t r = i - g * nel;
-  g += r < 0 ? -1 : (r >= nel ? 1 : 0);
-  return g;
-}
-
-// floor(a / d) for 0 <= a < 2^31, 1 <= d, from rd = 1 / d in float64 (the product is within one
-// of the quotient; one correction step), instead of an integer division sequence
-__device__ __forceinline__ int div_rcp(int a, int d, double rd) {
-  int q = (int)((double)a * rd);
-  const int r = a - q * d;
-  q += r < 0 ? -1 : (r >= d ? 1 : 0);
-  return q;
-}
-// a / p for the supported element degrees p = 2, 3, 4 (a >= 0): constant divisors
-__device__ __forceinline__ int div_p(int a, int p) { return p == 4 ? a >> 2 : (p == 2 ? a >> 1 : a / 3); }
-
-template <typename T, bool CPLX>
-__device__ __forceinline__ void assemble_one(const KP<T>& P, int64_t i, int nel, double rnel, int nc, int p, int n,
-                                             int P1, const CellCoef<T>& cf, int base_in_out);
-
-template <typename T, bool CPLX>
-__global__ __launch_bounds__(256) void fe_assemble_kernel(KBatch<T> kb, int nc, int p, int n, int P1, CellCoef<T> cf,
-                                                          int N, int base_in_out) {
-  const KP<T>& P = kb.k[blockIdx.z];
-  const int nel = CPLX ? P.nv : P.ncr;  // elements per row: complex pairs or real columns
-  const int64_t total = (int64_t)N * nel;
-  const double rnel = 1.0 / nel;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256)
-    assemble_one<T, CPLX>(P, i, nel, rnel, nc, p, n, P1, cf, base_in_out);
-}
-
-template <typename T, bool CPLX>
-__device__ __forceinline__ void assemble_one(const KP<T>& P, int64_t i, int nel, double rnel, int nc, int p, int n,
-                                             int P1, const CellCoef<T>& cf, int base_in_out) {
-  const int64_t g = row_of(i, nel, rnel);
-  const int j = (int)(i - g * nel);
-  const int gi = (int)g;
-  const int nn = n * n;
-  const int iz = div_rcp(gi, nn, 1.0 / nn), rem = gi - iz * nn, iy = div_rcp(rem, n, 1.0 / n), ix = rem - iy * n;
-  const int qx = div_p(ix, p), rx = ix - qx * p, qy = div_p(iy, p), ry = iy - qy * p, qz = div_p(iz, p),
-            rz = iz - qz * p;
-  const int S = nc * P1;
-  const int bx = qx * P1 + (rx ? rx + 1 : 0), by = qy * P1 + (ry ? ry + 1 : 0), bz = qz * P1 + (rz ? rz + 1 : 0);
-  const T msc = cf.mscale * cf.om[rx] * cf.om[ry] * cf.om[rz];
-  const T* __restrict__ Yc = P.ycell;
-  const int64_t ldc = P.ldc;
-  T alpha, c, beta;
-  step_scalars(P, alpha, c, beta);
-  // (ky, kz) slot pairs in a fixed order, each the lower-x slot then (shared x node) the next one
-  if constexpr (!CPLX) {
-    T s = 0;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int ky = kk & 1, kz = kk >> 1;
-      if ((ky && ry) || (kz && rz)) continue;
-      const int64_t r0 = bx + (int64_t)S * (by + ky + (int64_t)S * (bz + kz));
-      T add = Yc[r0 * ldc + j];
-      if (rx == 0) add += Yc[(r0 + 1) * ldc + j];
-      s += add;
-    }
-    const int64_t io = g * P.ldo + j;
-    const T base = base_in_out ? P.out[io] : (beta != T(0) ? -beta * P.prev[io] : T(0));
-    P.out[io] = alpha * (msc * s - c * P.x[g * P.ldx + j]) + base;
-  } else {
-    const Phase3<T> ph = P.ph;
-    C2<T> s{0, 0};
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int ky = kk & 1, kz = kk >> 1;
-      if ((ky && ry) || (kz && rz)) continue;
-      const int sy = by + ky, sz = bz + kz;
-      const int64_t r0 = bx + (int64_t)S * (sy + (int64_t)S * sz);
-      C2<T> z0{Yc[r0 * ldc + 2 * j], Yc[r0 * ldc + 2 * j + 1]};
-      C2<T> z1{0, 0};
-      if (rx == 0) z1 = C2<T>{Yc[(r0 + 1) * ldc + 2 * j], Yc[(r0 + 1) * ldc + 2 * j + 1]};
-      // periodic images: slot 0 of a dimension came from the last cell
-      if (bx == 0) z0 = cjmul(C2<T>{ph.re[0], ph.im[0]}, z0);
-      if (sy == 0) {
-        z0 = cjmul(C2<T>{ph.re[1], ph.im[1]}, z0);
-        z1 = cjmul(C2<T>{ph.re[1], ph.im[1]}, z1);
-      }
-      if (sz == 0) {
-        z0 = cjmul(C2<T>{ph.re[2], ph.im[2]}, z0);
-        z1 = cjmul(C2<T>{ph.re[2], ph.im[2]}, z1);
-      }
-      s.r += z0.r + z1.r;
-      s.i += z0.i + z1.i;
-    }
-    const int64_t io = g * P.ldo + 2 * j, ix2 = g * P.ldx + 2 * j;
-    C2<T> base{0, 0};
-    if (base_in_out) base = C2<T>{P.out[io], P.out[io + 1]};
-    else if (beta != T(0)) base = C2<T>{-beta * P.prev[io], -beta * P.prev[io + 1]};
-    P.out[io] = alpha * (msc * s.r - c * P.x[ix2]) + base.r;
-    P.out[io + 1] = alpha * (msc * s.i - c * P.x[ix2 + 1]) + base.i;
-  }
-}
-
-// Node stage of real operators in one kernel, fe_node_fused_kernel: one workgroup (4
-// waves) per coupling tile of kTileRows FE rows (tile_node) x 16 NB real columns computes part, the slot
-// gather and out = alpha (m^-1/2 sum_slots(Y) + Ht_t Z^O - c x) - beta prev.  Order within
-// the workgroup: one batch of loads (x tile, H tile, function list; float32 also the
-// first slot pair of the gather, which lands during the matrix-core phase), part on the
-// matrix cores, the gather, acc = m^-1/2 sum - c x, then Ht_t Z^O accumulated onto acc
-// from Z^O rows staged in LDS, with the previous iterate loaded beside them.
-// LDS of the node kernel: the tile's rows of X (its column block; reused afterwards
-// for chunks of up to kTileRows rows of Z^O), its dense block of m^-1/2 H^co, and the
-// tile's function list.
-// Row strides (in elements) of the node kernel's LDS tiles, padded to 16 mod 32 so that the
-// two row groups of a half-wave in the MFMA operand reads fall into disjoint banks.
-constexpr int lds_row_stride(int w) { return w + (((16 - w % 32) % 32) + 32) % 32; }
-
-constexpr int kNodeNBMax = 5;  // 16-column blocks per fused node workgroup (80 real columns: no spills)
-
-// Row stride of the coupling block in LDS for a tile of FP functions: padded to 16 mod 32
-// (lds_row_stride) unless that would keep two workgroups from sharing a CU's 160 KB of LDS;
-// then the largest odd stride that fits (hs_cap, at least FP).
-template <typename T, int NB>
-constexpr int node_hs_cap(int fpmax) {
-  const int budget = (80 * 1024 - 512) / (int)sizeof(T);  // elements per workgroup
-  const int cap = (budget - kTileRows * lds_row_stride(NB * 16) - fpmax * (int)sizeof(int32_t) / (int)sizeof(T)) /
-                  kTileRows;
-  return (cap & 1) ? cap : cap - 1;
-}
-__host__ __device__ constexpr int node_hs(int fp, int hs_cap) {
-  return lds_row_stride(fp) <= hs_cap || hs_cap < fp ? lds_row_stride(fp) : hs_cap;
-}
-template <typename T, int NB>
-constexpr size_t node_lds_bytes(int fpmax) {
-  return (size_t)kTileRows * (lds_row_stride(NB * 16) + node_hs(fpmax, node_hs_cap<T, NB>(fpmax))) * sizeof(T) +
-         (size_t)fpmax * sizeof(int32_t);
-}
-
-template <typename T, int NB>
-__global__ __launch_bounds__(256, NB == 4 ? 3 : 2) void fe_node_fused_kernel(KBatch<T> kb, int nc, int p, int n, int P1,
-                                                               CellCoef<T> cf, const int32_t* __restrict__ tile_fptr,
-                                                               const int32_t* __restrict__ tile_fns, int N, int ncb,
-                                                               int hs_cap, int tm) {
-  using M = Mfma<T>;
-  using V4 = typename M::V4;
-  constexpr int TR = kTileRows, CBW = NB * 16, XS = lds_row_stride(CBW);
-  constexpr int XPT = TR * CBW / 256;  // staged elements per thread of one TR x CBW block
-  extern __shared__ unsigned char smem_raw[];
-  const KP<T>& P = kb.k[blockIdx.z];
-  const int ncr = P.ncr;
-  // launch order: the column blocks of a tile are consecutive in L, and each XCD (workgroups
-  // bk = x mod 8) takes a contiguous range of L, so the column blocks that read the same
-  // coupling block and x rows share one L2
-  const int nbk = gridDim.x, bk = blockIdx.x, nb8 = nbk & ~7;
-  const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
-  const int t = L / ncb;
-  const int cb0 = (L - t * ncb) * CBW;
-  if (cb0 >= ncr) return;
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int li = lane & 15, lk = lane >> 4;
-  const int f0 = tile_fptr ? tile_fptr[t] : 0, FP = tile_fptr ? tile_fptr[t + 1] - f0 : 0;
-  const int HS = node_hs(FP, hs_cap);
-  T* xs = reinterpret_cast<T*>(smem_raw);  // [TR][XS]: x rows of the tile (zero past the mesh), later Z^O rows
-  T* hs = xs + TR * XS;                     // [TR][HS]: the tile's block
-  int32_t* fs = reinterpret_cast<int32_t*>(hs + __umul24(TR, HS));  // [FP]: enrichment function of each tile column
-  const T* __restrict__ tv = P.tv + (int64_t)f0 * TR;  // [TR][FP]
-  const T* __restrict__ zo = P.zo;                         // [n_enr][ncr]
-  const T* __restrict__ x = P.x;
-  const int64_t ldx = P.ldx;
-  const int64_t ldc = P.ldc;
-  T alpha, c, beta;
-  step_scalars(P, alpha, c, beta);
-  const T* prev = P.prev;  // may be the same array as out (each element is read before it is written)
-  T* out = P.out;
-  const int64_t ldo = P.ldo;
-  const int S = nc * P1;
-  // Global loads below are unconditional, from clamped in-bounds addresses, with
-  // unwanted values replaced by selects, so that each batch is issued at once.
-  int colc[NB];
-  bool colok[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const int col = cb0 + nb * 16 + li;
-    colok[nb] = col < ncr;
-    colc[nb] = colok[nb] ? col : ncr - 1;
-  }
-  // node-slot grid columns, not clamped: a row of the grid (ldc >= ncr; a multiple of 8, or 1) is
-  // followed by the next row or by the grid's padding (one row plus 16 kNodeNBMax elements,
-  // slot_grid_elems), so every column this block reads, below ncr + 16 NB, stays in the
-  // allocation; values past ncr only reach lanes whose output is not stored.  The loads of a
-  // row then differ by constant offsets.
-  const T* __restrict__ Ycl = P.ycell + cb0 + li;
-
-  // slots of node i per dimension: a shared node (i mod p == 0) has two, the one from
-  // the lower cell first; slot 0 holds the periodic image of the last cell
-  int bx[4], by[4], bz[4], gc[4];
-  bool x2[4], y2[4], z2[4], ok[4];
-  T msc[4];
-  int tx0, ty0, tz0;  // the tile's first node (uniform)
-  tile_origin(t, n, tm, tx0, ty0, tz0);
-  // consecutive rows (mode 0): the node of the tile's first row (uniform), the others by stepping
-  // along x from it, without a division per row
-  int sx0 = 0, sy0 = 0, sz0 = 0;
-  if (tm == 0) {
-    sz0 = tx0 / (n * n);
-    const int rem = tx0 - sz0 * n * n;
-    sy0 = rem / n;
-    sx0 = rem - sy0 * n;
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int r = w * 16 + M::row(lane, v);
-    int ix, iy, iz, gv;
-    if (tm == 0) {
-      gv = tx0 + r;
-      ix = sx0 + r;
-      iy = sy0;
-      iz = sz0;
-      while (ix >= n) {
-        ix -= n;
-        if (++iy == n) {
-          iy = 0;
-          ++iz;
+        for (int v = 0; v < 4; ++v) {
+          const NodeRow<T>& r = row(rb, v);
+          const T* ya = Y + r.slot + ((r.flags & kflags(kk)) == kflags(kk) ? kofs : 0);
+          a[rb][v] = load_cols<T, NC>(ya);
+          b[rb][v] = load_cols<T, NC>(ya + r.dx);
         }
       }
-      if (gv >= N) gv = -1, ix = iy = iz = 0;
-    } else {
-      gv = tile_row_coords(tx0, ty0, tz0, r, n, tm, ix, iy, iz);
-    }
-    ok[v] = gv >= 0;
-    gc[v] = ok[v] ? gv : 0;
-    const int qx = div_p(ix, p), rx = ix - qx * p, qy = div_p(iy, p), ry = iy - qy * p, qz = div_p(iz, p),
-              rz = iz - qz * p;
-    bx[v] = qx * P1 + (rx ? rx + 1 : 0);
-    by[v] = qy * P1 + (ry ? ry + 1 : 0);
-    bz[v] = qz * P1 + (rz ? rz + 1 : 0);
-    x2[v] = rx == 0;
-    y2[v] = ry == 0;
-    z2[v] = rz == 0;
-    msc[v] = cf.mscale * cf.om[rx] * cf.om[ry] * cf.om[rz];
-  }
-  // element offset of each row's first slot in the node-slot grid (one 64-bit product per
-  // row); the other slots of a node lie S ldc (y) and S^2 ldc (z) further (and ldc in x)
-  const int64_t Sl = (int64_t)S * ldc, S2l = Sl * S;
-  int64_t yoff[4];
+  };
+  auto pair_add = [&](int kk, const CV (&a)[RB][4], const CV (&b)[RB][4]) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) yoff[v] = (bx[v] + (int64_t)S * (by[v] + (int64_t)S * bz[v])) * ldc;
+    for (int rb = 0; rb < RB; ++rb)
+      if (need(rb, kk)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int f = row(rb, v).flags;
+          const CV q = pair_sum(f, row(rb, v).dx, kk, a[rb][v], b[rb][v]);
+          const T mn = (f & kflags(kk)) == kflags(kk) ? T(1) : T(0);
+#pragma unroll
+          for (int j = 0; j < NC; ++j) sa[rb][v].e[j] = fma(q.e[j], mn, sa[rb][v].e[j]);
+        }
+      }
+  };
 
-  // ---- one batch of loads: the x tile, the first part of the H tile, the function list
-  // and (real columns) the first slot pair of the gather, which lands during the
-  // matrix-core phase below
-  constexpr bool kEarly = sizeof(T) == 4;
-  // the whole H tile in the first batch for up to 48 (float64) / 32 (float32: its registers
-  // also hold the first gather loads) functions
-  constexpr int HPT = sizeof(T) == 8 ? 12 : 8;
-  const int nh = TR * FP;
-  T gA[4][NB], gB[4][NB];
-  // staging of a [TR][CBW] block: thread (tr, tc) = (threadIdx.x / 16, threadIdx.x % 16) takes
-  // rows tr + 16 i (i < TR / 16) and columns tc + 16 j (j < NB), element i NB + j
-  static_assert(TR == 64 && XPT == 4 * NB, "staging layout assumes 64-row tiles");
-  const int tr = (int)threadIdx.x >> 4, tc = (int)threadIdx.x & 15;
-  // tile rows past the mesh and columns past ncr are clamped for the loads (their values are
-  // not used); the staging rows of this thread: tr + 16 i
-  const int cmax = ncr - 1 - cb0;
-  const T* xrow[4];
-  bool rowok[4];
+  // ---- acc = m^-1/2 sum - c x (the two largest terms meet first, so that what is left of them is rounded
+  // at its own size), then acc += Ht_t Z^O over k-steps of 4 functions, KB steps of Z^O loaded ahead
+  constexpr int KB = 4;
+  const T* __restrict__ Zc = P.zo + colx;
+  auto zload = [&](int k0, CV (&z)[KB]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int gr = tile_row_node(tx0, ty0, tz0, tr + 16 * i, n, tm);
-    rowok[i] = gr >= 0;
-    xrow[i] = x + (int64_t)(rowok[i] ? gr : 0) * ldx + cb0;
-  }
-  // the H tile [TR][FP] on the same map, HJ 16-column groups per batch: rows tr + 16 i,
-  // columns jc0 + tc + 16 j (past FP: clamped loads, no store)
-  constexpr int HJ = HPT / 4;
-  auto hload = [&](int jc0, T (&hv)[HPT]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ro = (int)__umul24((unsigned)(tr + 16 * i), (unsigned)FP);
-#pragma unroll
-      for (int j = 0; j < HJ; ++j) hv[i * HJ + j] = tv[min(ro + jc0 + tc + 16 * j, nh - 1)];
+    for (int j = 0; j < KB; ++j) {
+      z[j] = load_cols<T, NC>(Zc + (int64_t)fs[min(k0 + 4 * j + lk, FP - 1)] * ncr);
+      fix_odd(z[j]);
     }
   };
-  auto hstore = [&](int jc0, const T (&hv)[HPT]) {
+  const T sz = (li & 1) ? T(1) : T(-1);  // NC = 1: sign of the partner's part
+  auto hz = [&](int k0, const CV (&z)[KB]) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ro = (int)__umul24((unsigned)(tr + 16 * i), (unsigned)HS);
+    for (int j = 0; j < KB; ++j) {
+      if (k0 + 4 * j >= FP) break;
+      const int f = k0 + 4 * j + lk;
 #pragma unroll
-      for (int j = 0; j < HJ; ++j) {
-        const int col = jc0 + tc + 16 * j;
-        if (col < FP) hs[ro + col] = hv[i * HJ + j];
-      }
-    }
-  };
-  {
-    T xv[XPT], hv[HPT];
+      for (int rb = 0; rb < RB; ++rb) {
+        const T* h = hs + (unsigned)(((rb0 + rb) * 16 + li) * HS + f) * E;
+        if constexpr (CPLX) {
+          const T hr = h[0], hi = h[1];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int j = 0; j < NB; ++j) xv[i * NB + j] = xrow[i][min(tc + 16 * j, cmax)];
-    }
-    if (FP > 0) hload(0, hv);
-    const int32_t fv = (int)threadIdx.x < FP ? tile_fns[f0 + threadIdx.x] : 0;
-    if constexpr (kEarly) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const T* ya = Ycl + yoff[v];
-        const T* yb = x2[v] ? ya + ldc : ya;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          gA[v][nb] = ya[nb * 16];
-          gB[v][nb] = yb[nb * 16];
-        }
-      }
-    }
-    if ((int)threadIdx.x < FP) fs[threadIdx.x] = fv;
-    for (int f = threadIdx.x + 256; f < FP; f += 256) fs[f] = tile_fns[f0 + f];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) xs[(tr + 16 * i) * XS + tc + 16 * j] = rowok[i] ? xv[i * NB + j] : T(0);
-    if (FP > 0) hstore(0, hv);
-  }
-  // the rest of the H tile
-  for (int jc0 = 16 * HJ; jc0 < FP; jc0 += 16 * HJ) {
-    T hv[HPT];
-    hload(jc0, hv);
-    hstore(jc0, hv);
-  }
-  __syncthreads();
-
-  // ---- part = Ht_t^* X_t from LDS: (function block mb, column block nb) pairs over the 4 waves
-  if (FP > 0) {
-    const int MB = (FP + 15) / 16;
-    // two (mb, nb) blocks per wave at a time: independent accumulator chains
-    for (int q0 = w; q0 < MB * NB; q0 += 8) {
-      const bool two = q0 + 4 < MB * NB;
-      int fcs[2], cls[2];
-      bool foks[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int q = (h == 0 || two) ? q0 + 4 * h : q0;
-        const int mb = q / NB, nb = q - mb * NB;
-        const int f = mb * 16 + li;
-        foks[h] = f < FP;
-        fcs[h] = foks[h] ? f : FP - 1;
-        cls[h] = nb * 16 + li;  // LDS column; past ncr it holds a duplicate, never stored
-      }
-      V4 pc[2] = {V4{0, 0, 0, 0}, V4{0, 0, 0, 0}};
-#pragma unroll 4
-      for (int ks = 0; ks < TR / 4; ++ks) {
-        const int r = ks * 4 + lk;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const T av = hs[__umul24(r, HS) + fcs[h]];
-          const T a = foks[h] ? av : T(0);
-          pc[h] = M::op(a, xs[__umul24(r, XS) + cls[h]], pc[h]);
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (h == 1 && !two) break;
-        const int q = q0 + 4 * h;
-        const int mb = q / NB;
-        const int col = cb0 + cls[h];
-        if (col < ncr) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int fi = mb * 16 + M::row(lane, v);
-            if (fi < FP) P.part[(int64_t)(f0 + fi) * ncr + col] = pc[h][v];
+          for (int i = 0; i < NC; ++i) acc[rb][i] = M::op(hr, z[j].e[i], acc[rb][i]);
+          if constexpr (NC == 2) {
+            acc[rb][0] = M::op(-hi, z[j].e[1], acc[rb][0]);
+            acc[rb][1] = M::op(hi, z[j].e[0], acc[rb][1]);
+          } else {
+            acc[rb][0] = M::op(hi, sz * __shfl_xor(z[j].e[0], 1), acc[rb][0]);
           }
+        } else {
+          const T hv = h[0];
+#pragma unroll
+          for (int i = 0; i < NC; ++i) acc[rb][i] = M::op(hv, z[j].e[i], acc[rb][i]);
         }
       }
     }
+  };
+  const bool ys = __any(fall & kY2), zs = __any(fall & kZ2);
+  {
+    CV a[RB][4], b[RB][4];
+    if (ys) {
+      pair_load(1, a, b);
+      pair_add(1, a, b);
+    }
+    if (zs) {
+      pair_load(2, a, b);
+      pair_add(2, a, b);
+    }
+    if (ys && zs) {
+      pair_load(3, a, b);
+      pair_add(3, a, b);
+    }
+  }
+  CV z[KB];
+  if (FP > 0) zload(0, z);
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const T msc = row(rb, v).msc;
+#pragma unroll
+      for (int j = 0; j < NC; ++j) acc[rb][j][v] = msc * sa[rb][v].e[j] - c * xr[rb][v].e[j];
+    }
+  for (int k0 = 0; k0 < FP; k0 += 4 * KB) {
+    CV zn[KB];
+    if (k0 + 4 * KB < FP) zload(k0 + 4 * KB, zn);
+    hz(k0, z);
+#pragma unroll
+    for (int j = 0; j < KB; ++j) z[j] = zn[j];
   }
 
-  // ---- node-slot gather: sum over the (up to 8) cell results stored for the node
-  T sum[4][NB];
+  // ---- out = alpha acc - beta prev; rows past the mesh: 0, not stored
 #pragma unroll
-  for (int v = 0; v < 4; ++v)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) sum[v][nb] = 0;
-  // masks as factors (the gathered values are finite): fma(v, 1, s) = v + s and fma(v, 0, s) = s
-  // exactly, so the sums equal those of the selects, without the selects
-  T m2[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) m2[v] = x2[v] ? T(1) : T(0);
-  if constexpr (kEarly) {
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const T mo = ok[v] ? T(1) : T(0);
+      const bool ok = row(rb, v).flags & kIn;
+      fix_odd(pv[rb][v]);
+      CV r;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) sum[v][nb] = fma(fma(gB[v][nb], m2[v], gA[v][nb]), mo, sum[v][nb]);
-    }
-  }
-  // (ky, kz) slot pairs in a fixed order; a pair is visited when some lane of the
-  // wave needs it, lanes that do not need it reload their first slot (in bounds,
-  // cached) and discard it
-#pragma unroll
-  for (int kk = kEarly ? 1 : 0; kk < 4; ++kk) {
-    const int ky = kk & 1, kz = kk >> 1;
-    bool need[4];
-    int anyv = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      need[v] = ok[v] && (ky == 0 || y2[v]) && (kz == 0 || z2[v]);
-      anyv |= need[v];
-    }
-    if (kk > 0 && !__any(anyv)) continue;
-    const int64_t kofs = ky * Sl + kz * S2l;  // slot offset of the pair (uniform)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const T* ya = Ycl + yoff[v] + (need[v] ? kofs : 0);
-      const T* yb = x2[v] ? ya + ldc : ya;
-      const T mn = need[v] ? T(1) : T(0);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const T v0 = ya[nb * 16];
-        const T v1 = yb[nb * 16];
-        sum[v][nb] = fma(fma(v1, m2[v], v0), mn, sum[v][nb]);
+      for (int j = 0; j < NC; ++j) {
+        r.e[j] = alpha * acc[rb][j][v];
+        if (use_prev) r.e[j] -= beta * pv[rb][v].e[j];
       }
-    }
-  }
-
-  // ---- acc = m^-1/2 sum - c x on the MFMA result layout, then acc += Ht_t Z^O
-  V4 acc[NB];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int rl = w * 16 + M::row(lane, v);
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb][v] = msc[v] * sum[v][nb] - c * xs[__umul24(rl, XS) + nb * 16 + li];
-  }
-  // the previous iterate is read here, before any element of out is written
-  T pv[4][NB];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const T* pr = prev + (int64_t)gc[v] * ldo;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) pv[v][nb] = beta != T(0) ? pr[colc[nb]] : T(0);
-  }
-
-  // Z^O rows of the tile's functions, in chunks of TR rows staged over the x tile
-  const int rA = w * 16 + li;
-  for (int fc0 = 0; fc0 < FP; fc0 += TR) {
-    const int FC = min(TR, FP - fc0);  // a multiple of 4, as FP is
-    __syncthreads();                   // the x tile (or the previous chunk) is no longer read
-    {
-      T zv[XPT];
-      int fnv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = tr + 16 * i;
-        fnv[i] = r < FC ? fs[fc0 + r] : -1;
-        const unsigned ro = __umul24((unsigned)max(fnv[i], 0), (unsigned)ncr) + (unsigned)cb0;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) zv[i * NB + j] = zo[ro + (unsigned)min(tc + 16 * j, cmax)];
+      T* o = P.out + row(rb, v).row * P.ldo + col;
+      if (ok && it.live) {
+        if (NC == 2 && col + 1 < ncr)
+          __builtin_memcpy(o, &r, sizeof(r));
+        else if (col < ncr)
+          o[0] = r.e[0];
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) xs[(tr + 16 * i) * XS + tc + 16 * j] = fnv[i] >= 0 ? zv[i * NB + j] : T(0);
+      for (int j = 0; j < NC; ++j) sa[rb][v].e[j] = ok ? r.e[j] : T(0);
     }
-    __syncthreads();
-#pragma unroll 2
-    for (int k0 = 0; k0 < FC; k0 += 4) {
-      const int f = k0 + lk;
-      const T a = hs[__umul24(rA, HS) + fc0 + f];
-      T b[NB];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) b[nb] = xs[__umul24(f, XS) + nb * 16 + li];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[nb] = M::op(a, b[nb], acc[nb]);
-    }
-  }
-
-  // ---- out = alpha acc - beta prev
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    T* orow = out + (int64_t)gc[v] * ldo;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      T r = alpha * acc[nb][v];
-      if (beta != T(0)) r -= beta * pv[v][nb];
-      if (ok[v] && colok[nb]) orow[colc[nb]] = r;
-    }
+  if (tile_fptr && (PX || pnext)) {
+    if constexpr (!PX) node_stash<T, NC>(xt, it, sa);
+    node_part<T, CPLX, NC>(P, hs, HS, xt, it);
   }
 }
 
 // Node stage of real operators at one column (the auxiliary-potential conjugate gradients,
 // Lanczos): one wave per coupling tile, lane = tile row, no LDS.  The slot gather takes the
-// same slots in the same order as fe_node_fused_kernel; the tile's coupling row is applied with
+// same slots in the same order as fe_node_kernel; the tile's coupling row is applied with
 // one product per function in list order, and each function's partial of H^co* x is a fixed
 // butterfly over the 64 rows.  Launched when every operator of the step has one column and the
 // tiles couple to at most kCol1MaxFunctions functions (per-function butterflies cost more than
@@ -1746,8 +1575,8 @@ constexpr int kCol1MaxFunctions = 24;  // functions per tile up to which one col
 template <typename T>
 __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc, int p, int n, int P1, CellCoef<T> cf,
                                                            const int32_t* __restrict__ tile_fptr,
-                                                           const int32_t* __restrict__ tile_fns, int ntiles, int tm) {
-  constexpr int TR = kTileRows;
+                                                           const int32_t* __restrict__ tile_fns, int ntiles, int tm,
+                                                           int pad) {
   const KP<T>& P = kb.k[blockIdx.z];
   const int t = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform per wave
   if (t >= ntiles) return;  // the whole wave
@@ -1784,7 +1613,7 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
   T acc = msc * sum - c * xv;
   if (tile_fptr) {
     const int f0 = tile_fptr[t], FP = tile_fptr[t + 1] - f0;  // a multiple of 4 (padded list)
-    const T* __restrict__ tv = P.tv + (int64_t)f0 * TR + (int64_t)r * FP;  // this row of the [TR][FP] block
+    const T* __restrict__ tv = P.tv + tile_offset(f0, t, pad) + (int64_t)r * (FP + pad);  // this row of the block
     // four functions at a time: their loads issued together, their butterflies interleaved
     for (int fb = 0; fb < FP; fb += 4) {
       T h[4], z[4], q[4];
@@ -1871,7 +1700,7 @@ __global__ __launch_bounds__(256) void enr_reduce1_kernel(KBatch<T> kb, int nch,
 // CPLX), 16x16 output tile per workgroup, LDS-staged K tiles.
 //   mode 0: zo = S x^O       mode 1: wp = (sum of the folded tile partials) + H^oo zo
 //   mode 2: out^O = alpha (S wp - c x^O) - beta prev^O
-//   mode 3: zo = S out^O      (Z^O of the next recurrence step)
+//   mode 3: zn = S out^O      (Z^O of the next recurrence step)
 template <typename T, bool CPLX>
 __global__ __launch_bounds__(256) void small_gemm_kernel(KBatch<T> kb, int mode, int64_t N, int n) {
   constexpr int E = CPLX ? 2 : 1;
@@ -1912,8 +1741,9 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(KBatch<T> kb, int mode,
   }
   if (i >= n || jc >= m) return;
   if (mode == 0 || mode == 3) {
-    P.zo[(int64_t)i * P.ncr + (int64_t)jc * E] = sr;
-    if (CPLX) P.zo[(int64_t)i * P.ncr + (int64_t)jc * E + 1] = si;
+    T* z = mode == 0 ? P.zo : P.zn;
+    z[(int64_t)i * P.ncr + (int64_t)jc * E] = sr;
+    if (CPLX) z[(int64_t)i * P.ncr + (int64_t)jc * E + 1] = si;
   } else if (mode == 1) {
     const T* p2 = P.part2 + (int64_t)i * P.nch * P.ncr + (int64_t)jc * E;
     T wr = 0, wi = 0;
@@ -1955,7 +1785,9 @@ constexpr size_t enr_chain_lds_bytes(int n) {
 }
 
 template <typename T, bool CPLX>
-__global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, int64_t N, int n, int next) {
+__global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, int64_t N, int n, int next,
+                                                         const int32_t* __restrict__ fn_pptr,
+                                                         const int32_t* __restrict__ fn_poff) {
   constexpr int E = CPLX ? 2 : 1, TC = kChainCols;
   extern __shared__ unsigned char chain_raw[];
   T* Ss = reinterpret_cast<T*>(chain_raw);  // [n][n] S
@@ -1996,7 +1828,34 @@ __global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, int64_t N
     }
   };
   // W'
-  if (m == 1) {
+  if (fn_pptr) {
+    // every function has at most kReduceChunk partials: folded here, in the order of enr_reduce1_kernel
+    for (int t = tid; t < n * TC; t += nth) {
+      const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
+      const int e0 = fn_pptr[i], cnt = fn_pptr[i + 1] - e0;
+      T wr[4], wi[4];
+#pragma unroll
+      for (int grp = 0; grp < 4; ++grp) {
+        T r[2] = {0, 0}, q[2] = {0, 0};  // even and odd entries of the group
+        for (int k = 0; grp + 4 * k < cnt; ++k) {
+          const T* v = P.part + (int64_t)fn_poff[e0 + grp + 4 * k] * ncr + (int64_t)j * E;
+          if (k & 1) {
+            r[1] += v[0];
+            if (CPLX) q[1] += v[1];
+          } else {
+            r[0] += v[0];
+            if (CPLX) q[0] += v[1];
+          }
+        }
+        wr[grp] = r[0] + r[1];
+        wi[grp] = q[0] + q[1];
+      }
+      T sr, si;
+      dot(Hs, Zs, i, jl, sr, si);
+      Ws[(size_t)t * E] = ((wr[0] + wr[1]) + (wr[2] + wr[3])) + sr;
+      if (CPLX) Ws[(size_t)t * E + 1] = ((wi[0] + wi[1]) + (wi[2] + wi[3])) + si;
+    }
+  } else if (m == 1) {
     // one column: the TC threads of a row, which would all compute the same entry, split its
     // chunks (thread jl adds chunks jl, jl + TC, ... in order) into Os, then add them in order
     for (int t = tid; t < n * TC; t += nth) {
@@ -2083,8 +1942,8 @@ __global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, int64_t N
     T sr, si;
     dot(Ss, Os, i, jl, sr, si);
     if (j < m) {
-      P.zo[(int64_t)i * ncr + (int64_t)j * E] = sr;
-      if (CPLX) P.zo[(int64_t)i * ncr + (int64_t)j * E + 1] = si;
+      P.zn[(int64_t)i * ncr + (int64_t)j * E] = sr;
+      if (CPLX) P.zn[(int64_t)i * ncr + (int64_t)j * E + 1] = si;
     }
   }
 }
@@ -2432,51 +2291,74 @@ void launch_cell(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, int cw, 
   }
 }
 
-template <typename T, int NBW, bool CPLX>
-void launch_coupling_w(const oefe_op_s* op, const KBatch<T>& kb, hipStream_t s) {
-  const size_t lds = coupling_lds_bytes<T, CPLX>(op->tile_fpmax);
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(&fe_coupling_kernel<T, NBW, CPLX>), lds) != hipSuccess) return;
-  hipLaunchKernelGGL((fe_coupling_kernel<T, NBW, CPLX>), dim3((unsigned)op->n_tiles, 1, (unsigned)kb.nk), dim3(256),
-                     lds, s, kb, op->d.tile_fptr, op->d.tile_fns, op->n, op->tile_mode);
-}
-
-// nbw: 16-column blocks per coupling wave (1 or 2)
-template <typename T, bool CPLX>
-void launch_coupling(const oefe_op_s* op, const KBatch<T>& kb, int nbw, hipStream_t s) {
-  switch (nbw) {
-    case 2: launch_coupling_w<T, 2, CPLX>(op, kb, s); break;
-    default: launch_coupling_w<T, 1, CPLX>(op, kb, s); break;
+// part kernel, or node kernel with part of this step's X (px) or of its result (pnext)
+enum class NodeRun { part, node_px, node, node_pnext };
+template <typename T, bool CPLX, int NC>
+int launch_node_nc(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRun run, hipStream_t s) {
+  NodeMesh g{op->nc, op->p, op->n, op->P1, (int)op->N, op->tile_mode, tile_count(op->n, op->tile_mode),
+             op->n_enr > 0 ? op->tile_fpmax : 0, op->tile_pad, 1, 1};
+  // Column groups per workgroup (W, two waves each; the tuner's, else 1, 2 or 4), and whether items run
+  // across tile ends (the blocks of up to ntl tiles in LDS) or tiles are padded to whole workgroups: the
+  // shape with the most waves resident on a CU (16 by their registers, and the LDS), less the padding's
+  // idle ones.  At equal counts 4 groups share a block in float64 (diamond64, 320 columns: 2930 us
+  // against 3560 with 2) and 2 in float32 (1430 against 1480).
+  const int G = (int)cdiv(max_ncr, 16 * NC);
+  const int fixed = op->tune_cb > 0 ? std::max(1, std::min(kNodeGroups, op->tune_cb / 16)) : 0;
+  int W = 1;
+  double best = 0;
+  for (int w : {1, 2, 4}) {
+    if (fixed && w != (fixed == 3 ? 2 : fixed)) continue;
+    int ntl = 1;
+    for (int q = 0; q < kb.nk; ++q) ntl = std::max(ntl, node_tiles((int)cdiv(kb.k[q].ncr, 16 * NC), w));
+    for (int span = 0; span < 2; ++span) {
+      const size_t l = node_lds<T, CPLX, NC>(g.fpmax, g.pad, span ? ntl : 1, w).total;
+      if (l > 160 * 1024) continue;
+      const double eff = span ? 1.0 : (double)G / (double)(cdiv(G, w) * w);
+      const double score = eff * 2 * w * std::min<int64_t>(8 / w, 160 * 1024 / (int64_t)l) +
+                           (w == (sizeof(T) == 8 ? 4 : 2) ? 1e-3 : 0.0);
+      if (score > best) {
+        best = score;
+        W = w;
+        g.span = span;
+        g.ntl = span ? ntl : 1;
+      }
+    }
   }
-}
-
-template <typename T, bool CPLX>
-void launch_assemble(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, bool base_in_out, hipStream_t s) {
-  const int64_t nel = CPLX ? max_ncr / 2 : max_ncr;
-  const int64_t blocks = std::min<int64_t>(cdiv(op->N * nel, 256), int64_t(1) << 22);
-  hipLaunchKernelGGL((fe_assemble_kernel<T, CPLX>), dim3((unsigned)blocks, 1, (unsigned)kb.nk),
-                     dim3(256), 0, s, kb, op->nc, op->p, op->n, op->P1, coef<T>(op), (int)op->N,
-                     base_in_out ? 1 : 0);
-}
-
-template <typename T, int NB>
-void launch_node_fused_nb(const oefe_op_s* op, const KBatch<T>& kb, int ncb, hipStream_t s) {
-  const size_t lds = node_lds_bytes<T, NB>(op->n_enr > 0 ? op->tile_fpmax : 0);
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(&fe_node_fused_kernel<T, NB>), lds) != hipSuccess) return;
-  hipLaunchKernelGGL((fe_node_fused_kernel<T, NB>), dim3((unsigned)((int64_t)tile_count(op->n, op->tile_mode) * ncb), 1u,
-                     (unsigned)kb.nk), dim3(256), lds, s, kb, op->nc, op->p, op->n, op->P1, coef<T>(op),
-                     op->n_enr > 0 ? op->d.tile_fptr : nullptr, op->d.tile_fns, (int)op->N, ncb,
-                     node_hs_cap<T, NB>(op->n_enr > 0 ? op->tile_fpmax : 0), op->tile_mode);
-}
-
-template <typename T>
-void launch_node_fused(const oefe_op_s* op, const KBatch<T>& kb, int NB, int ncb, hipStream_t s) {
-  switch (NB) {
-    case 1: launch_node_fused_nb<T, 1>(op, kb, ncb, s); break;
-    case 2: launch_node_fused_nb<T, 2>(op, kb, ncb, s); break;
-    case 3: launch_node_fused_nb<T, 3>(op, kb, ncb, s); break;
-    case 4: launch_node_fused_nb<T, 4>(op, kb, ncb, s); break;
-    default: launch_node_fused_nb<T, 5>(op, kb, ncb, s); break;
+  const size_t lds = node_lds<T, CPLX, NC>(g.fpmax, g.pad, g.ntl, W).total;
+  int64_t nwg = 1;
+  for (int q = 0; q < kb.nk; ++q) {
+    const int64_t gq = cdiv(kb.k[q].ncr, 16 * NC);
+    nwg = std::max(nwg, cdiv(g.ntiles * (g.span ? gq : cdiv(gq, W) * W), W));
   }
+  const int32_t* fptr = op->n_enr > 0 ? op->d.tile_fptr : nullptr;
+  const dim3 grid((unsigned)nwg, 1u, (unsigned)kb.nk), block(128 * W);
+  if (run == NodeRun::part) {
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(&fe_part_kernel<T, CPLX, NC>), lds) != hipSuccess)
+      return OEFE_EDEVICE;
+    hipLaunchKernelGGL((fe_part_kernel<T, CPLX, NC>), grid, block, lds, s, kb, g, fptr, op->d.tile_fns);
+    return OEFE_OK;
+  }
+  auto go = [&](auto kernel) {
+    if (allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds) != hipSuccess) return (int)OEFE_EDEVICE;
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, kb, g, coef<T>(op), fptr, op->d.tile_fns,
+                       run == NodeRun::node_pnext ? 1 : 0);
+    return (int)OEFE_OK;
+  };
+  if (run == NodeRun::node_px) return go(&fe_node_kernel<T, CPLX, NC, true>);
+  return go(&fe_node_kernel<T, CPLX, NC, false>);
+}
+
+// float32: two columns per lane, so that a wave's row segments fill 128-byte lines; a single real
+// column takes one per lane
+template <typename T, bool CPLX>
+int launch_node(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRun run, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    int min_ncr = max_ncr;
+    for (int q = 0; q < kb.nk; ++q) min_ncr = std::min(min_ncr, kb.k[q].ncr);
+    if (CPLX || min_ncr >= 2) return launch_node_nc<T, CPLX, 2>(op, kb, max_ncr, run, s);
+  }
+  if constexpr (sizeof(T) == 8 || !CPLX) return launch_node_nc<T, CPLX, 1>(op, kb, max_ncr, run, s);
+  return OEFE_EINVAL;
 }
 
 inline int reduce_chunks(const oefe_op_s* op) { return std::max(1, (int)cdiv(op->fn_smax, kReduceChunk)); }
@@ -2530,86 +2412,88 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
     });
   };
   const dim3 gg((unsigned)cdiv(max_nv, 16), (unsigned)cdiv(nO, 16), nk);
-  // the chain that folds the tile partials into W' and writes the enrichment rows of out
-  // (and, in an overlapped recurrence, Z^O of the next step), on stream se
-  auto side_chain = [&](hipStream_t se) {
+  const size_t clds = enr_chain_lds_bytes<T, CPLX>(nO);
+  const bool one_chain =
+      nO > 0 && clds <= 96 * 1024 &&
+      allow_dynamic_lds(reinterpret_cast<const void*>(&enr_chain_kernel<T, CPLX>), clds) == hipSuccess;
+  // few partials per function (small meshes): the chain folds them itself, one launch fewer
+  const bool direct = one_chain && op->fn_smax <= kReduceChunk;
+  // fold of the tile partials, and the chain that forms W' from it and writes the enrichment rows of
+  // out (and, in an overlapped recurrence, Z^O of the next step), on stream se
+  auto fold = [&](hipStream_t se) {
+    if (direct) return;
     const int nch = reduce_chunks(op);
     hipLaunchKernelGGL((enr_reduce1_kernel<T>), dim3((unsigned)(nO * nch), (unsigned)cdiv(max_ncr, 64), nk),
                        dim3(256), 0, se, kb, nch, op->d.fn_pptr, op->d.fn_poff);
-    const size_t clds = enr_chain_lds_bytes<T, CPLX>(nO);
-    if (clds <= 96 * 1024 &&
-        allow_dynamic_lds(reinterpret_cast<const void*>(&enr_chain_kernel<T, CPLX>), clds) == hipSuccess) {
+  };
+  auto chain = [&](hipStream_t se) {
+    if (one_chain) {
       hipLaunchKernelGGL((enr_chain_kernel<T, CPLX>), dim3((unsigned)cdiv(max_nv, kChainCols), 1, nk), dim3(1024), clds,
-                         se, kb, op->N, nO, (ovl && !ov->last) ? 1 : 0);
+                         se, kb, op->N, nO, (ovl && !ov->last) ? 1 : 0, direct ? op->d.fn_pptr : nullptr,
+                         op->d.fn_poff);
     } else {
       hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 1, op->N, nO);
       hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 2, op->N, nO);
       if (ovl && !ov->last) hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 3, op->N, nO);
     }
-    if (ovl) (void)hipEventRecord(ov->ev_zo, se);
   };
-  if constexpr (!CPLX) {
-    // Real operators: fused node kernel after the cell stage; the chain of step k runs on
-    // the side stream beside the cell stage of step k+1, whose node stage waits for it.
-    if (nO > 0 && (!ovl || ov->first)) hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, s, kb, 0, op->N, nO);
-    cell_stage();
-    // node workgroup width: 16-column blocks, all real columns up to the cap, else near-equal
-    // parts.  Built-in cap: 4 blocks in float64 (diamond meshes of 110 k and 885 k nodes: node
-    // stage 112 / 3650 us against 127 / 4470 us with 5), 5 in float32.
-    const int nbdef = sizeof(T) == 8 ? 4 : kNodeNBMax;
-    const int nbcap = std::max(1, std::min(kNodeNBMax, op->tune_cb > 0 ? op->tune_cb / 16 : nbdef));
-    const int nb_all = (int)cdiv(max_ncr, 16);
-    const int ncb = (int)cdiv(nb_all, nbcap);
-    const int NB = (int)cdiv(nb_all, ncb);
-    if (ovl && !ov->first) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);  // this step's Z^O
-    // one column: the flat kernel where tiles couple to few functions (the auxiliary-potential
-    // operator, one function per atom: 23 % less time per conjugate-gradient iteration on
-    // diamond64); the Kohn-Sham operator's ~50 functions per tile stay on the matrix cores
-    if (max_ncr == 1 && op->tile_fpmax <= kCol1MaxFunctions) {
+  // one column: the flat kernel where tiles couple to few functions (the auxiliary-potential
+  // operator, one function per atom: 23 % less time per conjugate-gradient iteration on
+  // diamond64); the Kohn-Sham operator's ~50 functions per tile stay on the matrix cores
+  const bool col1 = !CPLX && !ovl && max_ncr == 1 && op->tile_fpmax <= kCol1MaxFunctions;
+  // A recurrence forms each step's partials Ht_t^* X with the X that the previous step wrote, while it
+  // is in registers; its first step, from X itself, before the node stage.
+  const bool ahead = ovl;
+  int rc = OEFE_OK;
+  if (nO > 0 && (!ovl || ov->first)) {
+    hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, s, kb, 0, op->N, nO);
+    if (ahead) {
+      rc = launch_node<T, CPLX>(op, kb, max_ncr, NodeRun::part, s);
+      if (rc) return rc;
+      fold(s);
+      (void)hipEventRecord(ov->ev_node, s);
+      (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
+    }
+  }
+  // The chain of this step (folded partials, Z^O and enrichment rows are there) beside its cell and
+  // node stages: the next step's Z^O goes to a buffer of its own
+  if (nO > 0 && ahead) {
+    chain(ov->side);
+    if (direct) (void)hipEventRecord(ov->ev_zo, ov->side);  // the partials are read
+  }
+  cell_stage();
+  // this step's Z^O is there and its partials are folded
+  if (ovl && nO > 0 && (direct || !ov->first)) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);
+  if (col1) {
+    if constexpr (!CPLX) {
       const int ntiles = tile_count(op->n, op->tile_mode);
       timed(OEFE_TIMER_NODE, s, [&] {
         hipLaunchKernelGGL((fe_node_col1_kernel<T>), dim3((unsigned)cdiv(ntiles, 4), 1u, (unsigned)kb.nk), dim3(256), 0, s,
                            kb, op->nc, op->p, op->n, op->P1, coef<T>(op), op->n_enr > 0 ? op->d.tile_fptr : nullptr,
-                           op->d.tile_fns, ntiles, op->tile_mode);
+                           op->d.tile_fns, ntiles, op->tile_mode, op->tile_pad);
       });
-    } else {
-      timed(OEFE_TIMER_NODE, s, [&] { launch_node_fused<T>(op, kb, NB, ncb, s); });
-    }
-    if (nO > 0) {
-      hipStream_t se = s;
-      if (ovl) {
-        (void)hipEventRecord(ov->ev_node, s);
-        (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
-        se = ov->side;
-      }
-      side_chain(se);
-      if (ovl && ov->last) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);
     }
   } else {
-    // Bloch operators: the coupling kernel (and then the chain) on the side stream, after
-    // the previous step's node assembly and beside this step's cell stage; the assembly
-    // adds onto the coupling kernel's result in out.
-    if (nO > 0) {
-      hipStream_t se = s;
-      if (ovl) {
-        if (ov->first) (void)hipEventRecord(ov->ev_node, s);
-        (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
-        se = ov->side;
-      }
-      if (!ovl || ov->first) hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 0, op->N, nO);
-      const int cb = op->tune_cb;
-      const int nbw = cb >= 32 ? kCoupleNBWMax : 1;
-      timed(OEFE_TIMER_COUPLING, se, [&] { launch_coupling<T, CPLX>(op, kb, nbw, se); });
-      if (ovl) (void)hipEventRecord(ov->ev_k1, se);
-      side_chain(se);
-    }
-    cell_stage();
-    if (ovl) (void)hipStreamWaitEvent(s, ov->ev_k1, 0);
-    timed(OEFE_TIMER_NODE, s, [&] { launch_assemble<T, CPLX>(op, kb, max_ncr, nO > 0, s); });
-    if (ovl) {
+    // (a Bloch operator's node kernel is also its coupling stage)
+    const int kind = CPLX && nO > 0 && op->timer_kind == OEFE_TIMER_COUPLING ? OEFE_TIMER_COUPLING : OEFE_TIMER_NODE;
+    const NodeRun run = !ahead ? NodeRun::node_px : ov->last ? NodeRun::node : NodeRun::node_pnext;
+    timed(kind, s, [&] { rc = launch_node<T, CPLX>(op, kb, max_ncr, run, s); });
+    if (rc) return rc;
+  }
+  if (nO > 0 && ahead) {
+    // the fold of the next step's partials beside its cell stage
+    if (!ov->last) {
       (void)hipEventRecord(ov->ev_node, s);
+      (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
+      fold(ov->side);
+    }
+    if (!direct) {
+      (void)hipEventRecord(ov->ev_zo, ov->side);
       if (ov->last) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);
     }
+  } else if (nO > 0) {
+    fold(s);
+    chain(s);
   }
   return hipGetLastError() == hipSuccess ? OEFE_OK : OEFE_EDEVICE;
 }
@@ -2630,6 +2514,7 @@ KP<T> make_kp(const oefe_op_s* op, const T* x, int64_t ld, const T* prev, T* out
   P.ycell = (T*)w.ycell;
   P.ldc = w.ldc;
   P.zo = (T*)w.zo;
+  P.zn = (T*)w.zn;
   P.part = (T*)w.part;
   P.part2 = (T*)w.part2;
   P.nch = reduce_chunks(op);
@@ -2666,12 +2551,12 @@ void launch_density(const oefe_op_s* op, const T* x, int64_t ldx, int ncr, const
 
 }  // namespace
 
-// Node-slot grid elements: n_cells nd rows of ldc, then a padding of one row plus 16 kNodeNBMax
-// elements.  The fused node kernel reads the columns of a row without clamping them to ncr:
-// at most cb0 + 16 NB - 1 < ncr + 16 kNodeNBMax - 1 for a column block that starts below ncr,
-// so the reads past the last row's end stay inside the padding (ncr <= ldc).
+// Node-slot grid elements: n_cells nd rows of ldc, then a padding of one row plus 32 elements.  The
+// node kernel reads the columns of a row without clamping them to ncr: at most ncr + 30 for a group
+// of up to 32 columns that starts below ncr, so the reads past the last row's end stay inside the padding
+// (ncr <= ldc).
 static size_t slot_grid_elems(const oefe_op_s* op, int ldc) {
-  return (size_t)op->n_cells * op->nd * ldc + (size_t)ldc + 16 * kNodeNBMax;
+  return (size_t)op->n_cells * op->nd * ldc + (size_t)ldc + 32;
 }
 
 size_t step_work_bytes(const oefe_op_s* op, int elem_bytes, bool cplx, int nv, int* ldc_out) {
@@ -2684,7 +2569,7 @@ size_t step_work_bytes(const oefe_op_s* op, int elem_bytes, bool cplx, int nv, i
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   size_t bytes = 0;
   if (!op->diagonal) bytes += al(slot_grid_elems(op, ldc) * elem_bytes);
-  bytes += al((size_t)std::max(op->n_enr, 1) * ncr * elem_bytes);                 // zo
+  bytes += 2 * al((size_t)std::max(op->n_enr, 1) * ncr * elem_bytes);             // zo, zn
   bytes += al((size_t)std::max<int64_t>(op->tile_slots, 1) * ncr * elem_bytes);  // part
   bytes += al((size_t)std::max(op->n_enr, 1) * reduce_chunks(op) * ncr * elem_bytes);  // part2
   bytes += al((size_t)std::max(op->n_enr, 1) * ncr * elem_bytes);                 // wp
@@ -2704,6 +2589,8 @@ StepWork carve_step_work(const oefe_op_s* op, int elem_bytes, bool cplx, int nv,
     p += al(slot_grid_elems(op, ldc) * elem_bytes);
   }
   w.zo = p;
+  p += al((size_t)std::max(op->n_enr, 1) * ncr * elem_bytes);
+  w.zn = p;
   p += al((size_t)std::max(op->n_enr, 1) * ncr * elem_bytes);
   w.part = p;
   p += al((size_t)std::max<int64_t>(op->tile_slots, 1) * ncr * elem_bytes);
