@@ -1920,21 +1920,33 @@ int rowmul_inplace(double* X, int64_t ldx, int64_t n, int nv, const double* R, h
 // kernels (a pivot of the unit-diagonal matrix at or below n 2^-52, or a non-positive
 // diagonal before scaling); flag[0] holds the first failing index (INT32_MAX: none).
 template <bool CPLX>
+__global__ __launch_bounds__(1024) void cholbig_diag_kernel(const double* __restrict__ G, int ldg, int n,
+                                                            double* __restrict__ dsc, int32_t* __restrict__ flag) {
+  constexpr int E = CPLX ? 2 : 1;
+  __shared__ int bad;
+  if (threadIdx.x == 0) bad = INT32_MAX;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const double gii = G[((int64_t)i * ldg + i) * E];
+    if (!(gii > 0.0)) atomicMin(&bad, i);
+    dsc[i] = gii > 0.0 ? 1.0 / sqrt(gii) : 0.0;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = bad;
+}
+
+// The diagonal, which every row and column is scaled by, is read by the launch before: this one
+// overwrites it.
+template <bool CPLX>
 __global__ __launch_bounds__(256) void cholbig_scale_kernel(double* __restrict__ G, int ldg, int n,
-                                                            double* __restrict__ Rinv, double* __restrict__ dsc,
-                                                            int32_t* __restrict__ flag) {
+                                                            double* __restrict__ Rinv, const double* __restrict__ dsc) {
   constexpr int E = CPLX ? 2 : 1;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)n * n) return;
   const int i = (int)(t / n), j = (int)(t - (int64_t)i * n);
-  const double gii = G[((int64_t)i * ldg + i) * E], gjj = G[((int64_t)j * ldg + j) * E];
-  if (j == 0) {
-    if (!(gii > 0.0)) atomicMin(flag, i);
-    dsc[i] = gii > 0.0 ? 1.0 / sqrt(gii) : 0.0;
-  }
-  const double f = (gii > 0.0 && gjj > 0.0) ? 1.0 / (sqrt(gii) * sqrt(gjj)) : 0.0;
+  const double f = dsc[i] * dsc[j];
   double* g = G + ((int64_t)i * ldg + j) * E;
-  g[0] = i == j ? (gii > 0.0 ? 1.0 : 0.0) : g[0] * f;
+  g[0] = i == j ? (dsc[i] > 0.0 ? 1.0 : 0.0) : g[0] * f;
   if (CPLX) g[1] = i == j ? 0.0 : g[1] * f;
   double* r = Rinv + ((int64_t)i * n + j) * E;
   r[0] = i == j ? 1.0 : 0.0;
@@ -2002,16 +2014,16 @@ __global__ __launch_bounds__(256) void cholbig_final_kernel(const double* __rest
   }
 }
 
-__global__ void cholbig_init_kernel(int32_t* flag) { *flag = INT32_MAX; }
-
 static int chol_big(bool cplx, double* G, int ldg, int n, double* Rinv, double* dsc, int32_t* status, hipStream_t s) {
   int32_t* flag = status + 2;  // the status block has room beyond {code, column}
-  hipLaunchKernelGGL(cholbig_init_kernel, dim3(1), dim3(1), 0, s, flag);
   const unsigned g1 = (unsigned)cdiv((int64_t)n * n, 256);
-  if (cplx)
-    hipLaunchKernelGGL(cholbig_scale_kernel<true>, dim3(g1), dim3(256), 0, s, G, ldg, n, Rinv, dsc, flag);
-  else
-    hipLaunchKernelGGL(cholbig_scale_kernel<false>, dim3(g1), dim3(256), 0, s, G, ldg, n, Rinv, dsc, flag);
+  if (cplx) {
+    hipLaunchKernelGGL(cholbig_diag_kernel<true>, dim3(1), dim3(1024), 0, s, G, ldg, n, dsc, flag);
+    hipLaunchKernelGGL(cholbig_scale_kernel<true>, dim3(g1), dim3(256), 0, s, G, ldg, n, Rinv, dsc);
+  } else {
+    hipLaunchKernelGGL(cholbig_diag_kernel<false>, dim3(1), dim3(1024), 0, s, G, ldg, n, dsc, flag);
+    hipLaunchKernelGGL(cholbig_scale_kernel<false>, dim3(g1), dim3(256), 0, s, G, ldg, n, Rinv, dsc);
+  }
   for (int k = 0; k < n; ++k) {
     const dim3 g((unsigned)cdiv(n, 256), (unsigned)std::max(n - 1 - k, 1));
     if (cplx)
