@@ -1920,8 +1920,11 @@ int cholgs(oefe_op op, oefe_prec prec, void* X, int64_t ld, int32_t nv, void* wo
     }
     if (rowmul_on_mfma(cplx, nv)) {
       rc = rowmul_inplace(Xd, ld, op->n_tot, nv, L.Rinv, s);
+    } else if (cplx && nv >= 8 && rowmul_on_mfma(false, 2 * nv)) {  // in place, interleaved columns
+      rc = complex_as_real(L.Rinv, nv, nv, nv, L.gscr, s);
+      if (!rc) rc = rowmul_inplace(Xd, 2 * ld, op->n_tot, 2 * nv, L.gscr, s);
     } else {
-      rc = gemm_nn(cplx, Xd, ld, L.Rinv, nv, tmp, nv, op->n_tot, nv, nv, s);
+      rc = gemm_nn(cplx, Xd, ld, L.Rinv, nv, tmp, nv, op->n_tot, nv, nv, s, L.gscr);
       if (!rc) rc = copy_block(tmp, (int64_t)nv * E, Xd, ld * E, op->n_tot, nv * E, s);
     }
     if (rc) return fail(rc, "cholgs: kernel launch failed");
@@ -2013,7 +2016,7 @@ int rayleigh_ritz(oefe_op op, oefe_prec prec, void* Q, int64_t ld, int32_t nv, d
   if (!rc && rowmul_on_mfma(cplx, nv)) {
     rc = rowmul_inplace(Qd, ld, op->n_tot, nv, L.U, s);
   } else if (!rc) {
-    rc = gemm_nn(cplx, Qd, ld, L.U, nv, W, nv, op->n_tot, nv, nv, s);
+    rc = gemm_nn(cplx, Qd, ld, L.U, nv, W, nv, op->n_tot, nv, nv, s, nv >= 8 ? L.gscr : nullptr);
     if (!rc) rc = copy_block(W, (int64_t)nv * (cplx ? 2 : 1), Qd, ld * (cplx ? 2 : 1), op->n_tot, nv * (cplx ? 2 : 1), s);
   }
   // the eigensolver's status and the next pass's filter bounds, in stream order

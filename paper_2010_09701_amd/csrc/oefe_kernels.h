@@ -72,9 +72,12 @@ int density_final(const oefe_op_s* op, const double* dens, int nblk, double* dEd
 int gram(bool cplx, const double* A, int64_t lda, int na, const double* B, int64_t ldb, int nb, int64_t n,
          double* G, int ldg, double* scratch, size_t scratch_bytes, hipStream_t s);
 size_t gram_scratch_bytes(bool cplx, int na, int nb, int64_t n);
-// C = A * B, A [n x k] (lda), B [k x m] (ldb, small), C [n x m] (ldc)
+// C = A * B, A [n x k] (lda), B [k x m] (ldb, small), C [n x m] (ldc); scratch (complex, optional):
+// 4 k m doubles, with which wide blocks run on the matrix cores
 int gemm_nn(bool cplx, const double* A, int64_t lda, const double* B, int ldb, double* C, int64_t ldc, int64_t n,
-            int k, int m, hipStream_t s);
+            int k, int m, hipStream_t s, double* scratch = nullptr);
+// R [2k x 2m] <- the real matrix that multiplies interleaved complex rows as B [k x m] does
+int complex_as_real(const double* B, int ldb, int k, int m, double* R, hipStream_t s);
 // X <- X R in place on the matrix cores, X [n x nv] (ldx), R [nv x nv] row-major; real, nv <= 80
 bool rowmul_on_mfma(bool cplx, int nv);
 // (gate: device int; the product is skipped when it holds 0)

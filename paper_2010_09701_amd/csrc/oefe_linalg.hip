@@ -1310,8 +1310,9 @@ __global__ __launch_bounds__(64) void jacobi_vec_ring_kernel(const double* __res
 // (L_1 unit lower) and L_1^-1 in the right half; the Cholesky factor is L = L_1 D^1/2, so
 // L^-1 = D^-1/2 L_1^-1.  Step k reads only column k and row k, both final after step k - 1,
 // and writes neither, so one barrier per step suffices.  Thread t keeps column k + 1 + t % n
-// of the window and the rows k + 1 + t / n + r nth / n.  Same scaling, pivots and breakdown
-// rule as chol_lds_kernel; G is only read.
+// of the window and the rows k + 1 + t / n + r nth / n.  Jacobi scaling of the Gram matrix, pivots,
+// and breakdown when a pivot of the scaled (unit-diagonal) matrix is at or below n 2^-52; G is
+// only read.
 size_t chol_elim_lds_bytes(bool cplx, int n) { return ((size_t)n * (2 * n + 1) * (cplx ? 2 : 1) + n) * sizeof(double); }
 bool chol_elim_fits(bool cplx, int n) { return n <= 512 && chol_elim_lds_bytes(cplx, n) <= 158 * 1024; }
 
@@ -1422,116 +1423,132 @@ __global__ __launch_bounds__(1024) void chol_elim_kernel(const double* __restric
   }
 }
 
-// ---- Cholesky of the Jacobi-scaled Gram matrix and triangular inverse in LDS (small n).
-// Jacobi scaling of the Gram matrix, pivots, and breakdown when a pivot of the scaled
-// (unit-diagonal) matrix is at or below n 2^-52; G is only read.
-template <bool CPLX>
-__global__ __launch_bounds__(512) void chol_lds_kernel(const double* __restrict__ G, int ldg, int n,
-                                                       double* __restrict__ Rinv, double* __restrict__ dsc,
-                                                       int32_t* __restrict__ status) {
-  constexpr int E = CPLX ? 2 : 1;
-  extern __shared__ double sm[];
-  double* L = sm;                        // [n][n] lower factor (row-major)
-  double* Li = L + (size_t)n * n * E;    // [n][n] its inverse (lower)
-  double* d = Li + (size_t)n * n * E;    // [n] Jacobi scaling
+// ---- The same elimination with the matrix in registers, for the sizes whose [A | I] outgrows LDS
+// (complex 71..128, real 101..160 columns).  Left column k is dead after step k and right column k empty
+// before it, so one n x n array holds both: at step k its column k becomes the right one.  Thread
+// (ty, tx) of 32 x 32 keeps the entries (ty + 32 a, tx + 32 b); the owners of row and column k + 1
+// publish them in LDS as step k leaves them (two buffers, one barrier a step), with f_i = 0 for finished
+// rows and s_k = 1, so that the update is the same everywhere.  A step is a chain of about 1.1 us
+// (barrier, LDS reads, the division by the pivot, the update, publishing): 96 complex columns take
+// 105 us, against 340 with one launch per step.  16 x 16 threads are slower (130 us), and below the
+// limits so is this kernel (real 72 columns: 54 us, 42 above).
+bool chol_reg_fits(bool cplx, int n) { return n <= (cplx ? 128 : 160); }
+
+template <bool CPLX, int NB>
+__global__ __launch_bounds__(1024) void chol_reg_kernel(const double* __restrict__ G, int ldg, int n,
+                                                         double* __restrict__ Rinv, double* __restrict__ dsc,
+                                                         int32_t* __restrict__ status) {
+  constexpr int E = CPLX ? 2 : 1, T = 32, N = T * NB;
+  __shared__ double d[N], D[N];                    // Jacobi scaling, pivots
+  __shared__ double col[2][N * E], row[2][N * E];  // column k (rows > k) and row k of step k
   __shared__ int bad;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  if (tid == 0) bad = -1;
+  const int tid = threadIdx.x, tx = tid % T, ty = tid / T;
+  const int wrow = __builtin_amdgcn_readfirstlane(ty) + 64 / T - 1;  // the wave's last row of a block
+  if (tid == 0) bad = INT32_MAX;
   __syncthreads();
-  for (int i = tid; i < n; i += nth) {
-    const double gii = G[((int64_t)i * ldg + i) * E];
-    if (!(gii > 0.0)) atomicMax(&bad, i);
+  for (int i = tid; i < N; i += T * T) {
+    const double gii = i < n ? G[((int64_t)i * ldg + i) * E] : 1.0;
+    if (!(gii > 0.0)) atomicMin(&bad, i);
     d[i] = gii > 0.0 ? 1.0 / sqrt(gii) : 0.0;
-    dsc[i] = d[i];
+    if (i < n) dsc[i] = d[i];
   }
   __syncthreads();
-  if (bad >= 0) {
-    if (tid == 0) { status[0] = OEFE_ENOTSPD; status[1] = bad; }
-    return;
-  }
-  for (int t = tid; t < n * n; t += nth) {
-    const int i = t / n, j = t - i * n;
-    const double sc = d[i] * d[j];
-    L[(int64_t)t * E] = G[((int64_t)i * ldg + j) * E] * sc;
-    if (CPLX) L[(int64_t)t * E + 1] = G[((int64_t)i * ldg + j) * E + 1] * sc;
-    Li[(int64_t)t * E] = 0.0;
-    if (CPLX) Li[(int64_t)t * E + 1] = 0.0;
-  }
+  double ar[NB][NB], ai[NB][NB];
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int i = ty + T * a, j = tx + T * b;
+      const bool in = i < n && j < n;
+      const double* g = G + ((int64_t)(in ? i : 0) * ldg + (in ? j : 0)) * E;
+      const double sc = in ? d[i] * d[j] : 0.0;
+      ar[a][b] = in ? g[0] * sc : 0.0;
+      ai[a][b] = (CPLX && in) ? g[E - 1] * sc : 0.0;
+    }
+  auto publish = [&](int k) {
+    double *c = col[k & 1], *r = row[k & 1];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (k / T == b && tx == k % T) {
+#pragma unroll
+        for (int a = 0; a < NB; ++a) {
+          const int i = ty + T * a;
+          c[i * E] = i > k ? ar[a][b] : 0.0;
+          if (CPLX) c[i * E + E - 1] = i > k ? ai[a][b] : 0.0;
+          if (i == k) D[k] = ar[a][b];
+          if (i > k) ar[a][b] = ai[a][b] = 0.0;
+        }
+      }
+#pragma unroll
+    for (int a = 0; a < NB; ++a)
+      if (k / T == a && ty == k % T) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const int j = tx + T * b;
+          r[j * E] = j == k ? 1.0 : ar[a][b];
+          if (CPLX) r[j * E + E - 1] = j == k ? 0.0 : ai[a][b];
+        }
+      }
+  };
+  publish(0);
   __syncthreads();
-  auto re = [&](int i, int j) -> double& { return L[((int64_t)i * n + j) * E]; };
-  auto im = [&](int i, int j) -> double& { return L[((int64_t)i * n + j) * E + (E - 1)]; };
-  for (int k = 0; k < n; ++k) {
-    // breakdown: a pivot of the unit-diagonal (Jacobi-scaled) Gram matrix at or below
-    // n * 2^-52, i.e. numerically rank deficient in float64 (every thread sees the same value)
-    const double dk = re(k, k);
+  int fail = bad;  // a diagonal entry that is not positive
+  for (int k = 0; k < n && fail == INT32_MAX; ++k) {
+    const double dk = D[k];  // every thread sees the same value
+    const double *c = col[k & 1], *r = row[k & 1];
+    double sr[NB], si[NB], cr[NB], ci[NB];  // all reads of the step at once
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      sr[b] = r[(tx + T * b) * E];
+      si[b] = CPLX ? r[(tx + T * b) * E + E - 1] : 0.0;
+      cr[b] = c[(ty + T * b) * E];
+      ci[b] = CPLX ? c[(ty + T * b) * E + E - 1] : 0.0;
+    }
     if (!(dk > n * 2.220446049250313e-16) || !isfinite(dk)) {
-      if (tid == 0) bad = k;
+      fail = k;
       break;
     }
-    const double l = sqrt(dk);
-    for (int i = k + 1 + tid; i < n; i += nth) {
-      re(i, k) /= l;
-      if (CPLX) im(i, k) /= l;
-    }
-    __syncthreads();
-    const int m = n - k - 1;
-    for (int t = tid; t < m * m; t += nth) {
-      const int ii = t / m, jj = t - ii * m;
-      if (jj > ii) continue;
-      const int i = k + 1 + ii, j = k + 1 + jj;
-      if constexpr (!CPLX) {
-        re(i, j) -= re(i, k) * re(j, k);
-      } else {
-        const double ar = re(i, k), ai = im(i, k), br = re(j, k), bi = im(j, k);
-        re(i, j) -= ar * br + ai * bi;
-        im(i, j) -= ai * br - ar * bi;
+    const double rk = 1.0 / dk;
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      if (wrow + T * a <= k) continue;  // finished rows
+      const double fr = cr[a] * rk, fi = ci[a] * rk;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        if constexpr (!CPLX) {
+          ar[a][b] = fma(-fr, sr[b], ar[a][b]);
+        } else {
+          ar[a][b] -= fr * sr[b] - fi * si[b];
+          ai[a][b] -= fr * si[b] + fi * sr[b];
+        }
       }
     }
-    if (tid == 0) {
-      re(k, k) = l;
-      if (CPLX) im(k, k) = 0.0;
-    }
+    if (k + 1 < n) publish(k + 1);
     __syncthreads();
   }
-  __syncthreads();
-  if (bad >= 0) {
-    if (tid == 0) { status[0] = OEFE_ENOTSPD; status[1] = bad; }
+  if (fail != INT32_MAX) {
+    if (tid == 0) {
+      status[0] = OEFE_ENOTSPD;
+      status[1] = fail;
+    }
     return;
   }
-  // L^-1 row by row: Li[i][j] = -(sum_{k=j}^{i-1} L[i][k] Li[k][j]) / L[i][i], Li[i][i] = 1 / L[i][i];
-  // 8 lanes per entry, partial sums combined by lane shuffles
-  const int sub = tid & 7;
-  for (int i = 0; i < n; ++i) {
-    const double lii = re(i, i);
-    for (int j0 = 0; j0 <= i; j0 += nth / 8) {
-      const int j = j0 + (tid >> 3);
-      double sr = 0.0, si = 0.0;
-      if (j < i)
-        for (int k = j + sub; k < i; k += 8) {
-          const double lr = re(i, k), lm = CPLX ? im(i, k) : 0.0;
-          const double yr = Li[((int64_t)k * n + j) * E], yi = CPLX ? Li[((int64_t)k * n + j) * E + 1] : 0.0;
-          sr += lr * yr - lm * yi;
-          si += lr * yi + lm * yr;
-        }
-      for (int o = 4; o > 0; o >>= 1) {
-        sr += __shfl_xor(sr, o, 8);
-        si += __shfl_xor(si, o, 8);
-      }
-      if (sub == 0 && j <= i) {
-        Li[((int64_t)i * n + j) * E] = (j == i ? 1.0 : -sr) / lii;
-        if (CPLX) Li[((int64_t)i * n + j) * E + 1] = (j == i ? 0.0 : -si) / lii;
-      }
+  // Rinv = diag(d) L^-*, L^-1 = D^-1/2 L_1^-1: Rinv[j][i] = d_j conj(l_ij) / sqrt(D_i), i >= j
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int i = ty + T * a, j = tx + T * b;
+      if (i >= n || j >= n) continue;
+      const double sc = d[j] / sqrt(D[i]);
+      double* o = Rinv + ((int64_t)j * n + i) * E;
+      o[0] = i == j ? sc : (i > j ? sc * ar[a][b] : 0.0);
+      if (CPLX) o[E - 1] = i > j ? -sc * ai[a][b] : 0.0;
     }
-    __syncthreads();
+  if (tid == 0) {
+    status[0] = 0;
+    status[1] = -1;
   }
-  // Rinv = diag(d) Linv^*: Rinv[i][j] = d_i conj(Li[j][i]) (upper triangular)
-  for (int t = tid; t < n * n; t += nth) {
-    const int i = t / n, j = t - i * n;
-    const double* y = Li + ((int64_t)j * n + i) * E;
-    Rinv[(int64_t)t * E] = d[i] * y[0];
-    if (CPLX) Rinv[(int64_t)t * E + 1] = -d[i] * y[1];
-  }
-  if (tid == 0) { status[0] = 0; status[1] = -1; }
 }
 
 template <bool CPLX>
@@ -1777,7 +1794,26 @@ static bool gram_pairs(const double* A, int64_t lda, int na, const double* B, in
   return true;
 }
 
+// Complex blocks of at least 8 columns go through the real matrix-core Gram of their interleaved
+// columns: A^* B from the four real products re.re, re.im, im.re, im.im of each pair, which are the
+// entries of a real 2 na x 2 nb Gram matrix (as many multiplications as the complex one; with A = B half
+// of them by symmetry).  110 k rows, 96 columns: 290 + 36 -> 187 + 12 us (partials, reduction).
+static bool gram_as_real(bool cplx, int na, int nb) { return cplx && na >= 8 && nb >= 8; }
+static size_t gram_real_bytes(int na, int nb) { return ((size_t)4 * na * nb * sizeof(double) + 255) / 256 * 256; }
+
+__global__ __launch_bounds__(256) void gram_combine_kernel(const double* __restrict__ R, int na, int nb,
+                                                           double* __restrict__ G, int ldg) {
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (t >= na * nb) return;
+  const int i = t / nb, j = t - i * nb;
+  const double* r0 = R + (int64_t)(2 * i) * 2 * nb + 2 * j;
+  const double* r1 = r0 + 2 * nb;
+  G[((int64_t)i * ldg + j) * 2] = r0[0] + r1[1];
+  G[((int64_t)i * ldg + j) * 2 + 1] = r0[1] - r1[0];
+}
+
 size_t gram_scratch_bytes(bool cplx, int na, int nb, int64_t n) {
+  if (gram_as_real(cplx, na, nb)) return gram_real_bytes(na, nb) + gram_scratch_bytes(false, 2 * na, 2 * nb, n);
   if (gram_mfma_tiled(cplx, na, nb)) {
     const int gi = (int)cdiv(na, 16 * kGramNBMax), gj = (int)cdiv(nb, 16 * kGramNBMax);
     const int bi = (int)cdiv(na, gi), bj = (int)cdiv(nb, gj), gs = std::max(bi, bj);
@@ -1815,6 +1851,15 @@ static void launch_gram_mfma(const double* A, int64_t lda, int na, const double*
 int gram(bool cplx, const double* A, int64_t lda, int na, const double* B, int64_t ldb, int nb, int64_t n, double* G,
          int ldg, double* scratch, size_t scratch_bytes, hipStream_t s) {
   if (gram_scratch_bytes(cplx, na, nb, n) > scratch_bytes) return OEFE_EINVAL;
+  if (gram_as_real(cplx, na, nb)) {
+    const size_t rb = gram_real_bytes(na, nb);
+    const int rc = gram(false, A, 2 * lda, 2 * na, B, 2 * ldb, 2 * nb, n, scratch, 2 * nb, scratch + rb / sizeof(double),
+                        scratch_bytes - rb, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(gram_combine_kernel, dim3((unsigned)cdiv((int64_t)na * nb, 256)), dim3(256), 0, s, scratch, na, nb,
+                       G, ldg);
+    return check();
+  }
   if (gram_on_mfma(cplx, na, nb)) {
     launch_gram_mfma(A, lda, na, B, ldb, nb, n, G, ldg, scratch, s);
     return check();
@@ -1862,10 +1907,36 @@ int gram(bool cplx, const double* A, int64_t lda, int na, const double* B, int64
   return check();
 }
 
+// B (k x m complex) as the real 2k x 2m matrix that multiplies interleaved rows: row 2i holds (re, im)
+// pairs of B's row i, row 2i + 1 the pairs (-im, re)
+__global__ __launch_bounds__(256) void complex_as_real_kernel(const double* __restrict__ B, int ldb, int k, int m,
+                                                              double* __restrict__ R) {
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (t >= k * m) return;
+  const int i = t / m, j = t - i * m;
+  const double re = B[((int64_t)i * ldb + j) * 2], im = B[((int64_t)i * ldb + j) * 2 + 1];
+  double* r = R + (int64_t)(2 * i) * 2 * m + 2 * j;
+  r[0] = re;
+  r[1] = im;
+  r[2 * m] = -im;
+  r[2 * m + 1] = re;
+}
+int complex_as_real(const double* B, int ldb, int k, int m, double* R, hipStream_t s) {
+  hipLaunchKernelGGL(complex_as_real_kernel, dim3((unsigned)cdiv((int64_t)k * m, 256)), dim3(256), 0, s, B, ldb, k, m, R);
+  return check();
+}
+
 int gemm_nn(bool cplx, const double* A, int64_t lda, const double* B, int ldb, double* C, int64_t ldc, int64_t n,
-            int k, int m, hipStream_t s) {
+            int k, int m, hipStream_t s, double* scratch) {
+  if (cplx && scratch && k >= 8 && m >= 32 && n >= 4096) {
+    // wide complex blocks: the real matrix-core product of the interleaved columns (110 k rows, 96
+    // columns: 226 -> 198 us)
+    if (int rc = complex_as_real(B, ldb, k, m, scratch, s)) return rc;
+    return gemm_nn(false, A, 2 * lda, scratch, 2 * m, C, 2 * ldc, n, 2 * k, 2 * m, s);
+  }
   if (!cplx && k >= 16 && m >= 64 && n >= 4096) {  // real wide blocks: on the matrix cores
-    const int nbj = m >= 80 ? 5 : cdiv(m, 16);
+    // 5 or 4 blocks of 16 columns a workgroup, whichever pads m less (192 columns: 255 -> 205 us with 4)
+    const int nbj = cdiv(m, 64) * 4 < cdiv(m, 80) * 5 ? 4 : 5;
     const int ncb = cdiv(m, 16 * nbj);
     const dim3 g((unsigned)(cdiv(n, 128) * ncb));
     switch (nbj) {
@@ -2053,15 +2124,13 @@ int chol_factor_inverse(bool cplx, double* G, int ldg, int n, double* Rinv, int3
       hipLaunchKernelGGL(chol_elim_kernel<false>, dim3(1), dim3(1024), lds, s, G, ldg, n, Rinv, dsc, status, gate, go);
     return check();
   }
-  const size_t lds = ((size_t)2 * n * n * (cplx ? 2 : 1) + n) * sizeof(double);
-  if (lds <= 150 * 1024) {
-    const void* fn = cplx ? (const void*)chol_lds_kernel<true> : (const void*)chol_lds_kernel<false>;
-    if (allow_dynamic_lds(fn, lds) != hipSuccess) return OEFE_EDEVICE;
-    if (cplx)
-      hipLaunchKernelGGL(chol_lds_kernel<true>, dim3(1), dim3(512), lds, s, G, ldg, n, Rinv, dsc, status);
-    else
-      hipLaunchKernelGGL(chol_lds_kernel<false>, dim3(1), dim3(512), lds, s, G, ldg, n, Rinv, dsc, status);
-    return check();
+  if (chol_reg_fits(cplx, n)) {
+    auto run = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, G, ldg, n, Rinv, dsc, status);
+      return check();
+    };
+    if (cplx) return n <= 96 ? run(chol_reg_kernel<true, 3>) : run(chol_reg_kernel<true, 4>);
+    return n <= 128 ? run(chol_reg_kernel<false, 4>) : run(chol_reg_kernel<false, 5>);
   }
   return chol_big(cplx, G, ldg, n, Rinv, dsc, status, s);
 }
