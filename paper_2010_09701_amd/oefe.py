@@ -563,7 +563,7 @@ def band_energy_grad(op: Operator, X: torch.Tensor, f: torch.Tensor, want_dV: bo
     f = f.to(device=X.device, dtype=torch.float64).contiguous()
     E = torch.empty((), dtype=torch.float64, device=X.device)
     dV = torch.empty(op.n_cells, op.nq, dtype=torch.float64, device=X.device) if want_dV else None
-    dX = torch.empty_like(X) if want_dX else None
+    dX = torch.empty_strided(X.shape, X.stride(), dtype=X.dtype, device=X.device) if want_dX else None  # X's ld
     w = op.work(prec, nv)
     _check(_lib.band_energy_grad(op.handle, prec, _ptr(X), ld, nv, _ptr(f), _ptr(E), _ptr(dV), _ptr(dX), _ptr(w),
                                  _stream()), "band_energy_grad")
