@@ -142,7 +142,7 @@ Layout layout(const oefe_op_s* op, int prec, int nv, void* work) {
   L.U = (double*)p; p += sq;
   L.lam = (double*)p; p += al256(nv * sizeof(double));
   const size_t gs = al256(std::max(gram_scratch_bytes(cplx, nv, nv, op->n_tot),
-                                   (size_t)128 * nv * sizeof(double)));
+                                   dot_scratch_bytes(nv)));
   L.gscr = (double*)p; p += gs;
   L.jscr = (double*)p; p += al256(jacobi_scratch_bytes(cplx, nv));
   L.misc = (double*)p; p += 512 * sizeof(double);

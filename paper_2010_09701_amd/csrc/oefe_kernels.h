@@ -105,7 +105,9 @@ int max_offdiag_identity(bool cplx, const double* G, int n, double* err, hipStre
 int hermitian_part(bool cplx, double* G, int n, hipStream_t s, const int32_t* gate = nullptr);
 // copies / casts between blocks [n_rows x ld] (only the first ncols real columns)
 int copy_block(const double* src, int64_t lds, double* dst, int64_t ldd, int64_t n_rows, int ncols, hipStream_t s);
-// out = sum_j f_j Re sum_g conj(A[g][j]) B[g][j]  (f may be null: all ones), accumulated in float64
+// out = sum_j f_j Re sum_g conj(A[g][j]) B[g][j]  (f may be null: all ones), accumulated in float64;
+// scratch: dot_scratch_bytes(nv), or 1 KiB for one column
+size_t dot_scratch_bytes(int nv);
 template <typename T>
 int dot_columns(bool cplx, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n, int nv, const double* f,
                 double* out, double* scratch, hipStream_t s);
