@@ -573,9 +573,12 @@ int upload_operator(oefe_op_s* op, std::string& err) {
       // partials of the potential part of H^co per (flattened support cell, local node, function)
       if ((rc = dalloc(&op->d.hpart, (size_t)boff[nb] * op->nd * op->FMAX * E, err))) return rc;
       op->n_cf = boff[nb];
-      // H^oo's potential part in chunks of each block pair's common cells: about 2048 workgroups
-      op->hoo_nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(64, 2048 / ((int64_t)nb * nb)));
-      if ((rc = dalloc(&op->d.hoo_part, (size_t)nb * nb * op->hoo_nchunk * op->FMAX * op->FMAX * E, err))) return rc;
+      // H^oo's potential part in chunks of each block pair's common cells.  Pairs of neighbours hold
+      // nearly all of them, so many pairs are cut as finely as few, up to 64 k workgroups.
+      const int64_t npair = (int64_t)nb * (nb + 1) / 2;
+      op->hoo_nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(64, 65536 / npair));
+      if (op->hoo_nchunk > 8) op->hoo_nchunk &= ~7;
+      if ((rc = dalloc(&op->d.hoo_part, (size_t)npair * op->hoo_nchunk * op->FMAX * op->FMAX * E, err))) return rc;
     }
     if ((rc = dput(&op->d.blk_fn0, fn0, err))) return rc;
     if ((rc = dput(&op->d.blk_nf, nf, err))) return rc;
@@ -873,10 +876,13 @@ __global__ __launch_bounds__(256) void hco_rebuild_kernel(HcoRebuild a) {
 
 // H^oo = kinetic part + sum over the common support cells (ascending) of two blocks and their
 // quadrature points (the Gauss points, or the adaptive rule's points) of w V conj(N^O_i) N^O_j.
-// One workgroup per (block pair (bi, bj), chunk of their common cells): thread t takes the entry
-// item = t mod (nf_i nf_j) and the point lane t / (nf_i nf_j), lanes striding over each cell's
-// points; the lanes' sums are added in lane order into the chunk's partial, and
-// hoo_sum_kernel adds the chunks in order (a fixed summation order throughout).
+// One workgroup per (block pair bi <= bj, chunk of their common cells): thread t takes the entries
+// (f, all g) of function f = t mod F of block i and the point lane t / F, lanes striding over each
+// cell's points; the lanes' sums are added in lane order into the chunk's partial, and
+// hoo_sum_kernel adds the chunks in order and mirrors the pairs (a fixed summation order throughout).
+// Bound by the reads of N^O, F of block j and one of block i for F products per thread and point, which
+// the lanes of one point share: on 8 atoms (36 pairs, 37 k common cells of 125 points, F = 5) 450 us
+// with a thread per (entry, point), two reads for one product, over all ordered pairs; 96 us so.
 struct HooPair {
   const double *W, *V, *phi;  // the Gauss rule
   const int32_t* cf_cell;
@@ -892,60 +898,71 @@ struct HooPair {
   int nO, nb, FMAX, nq, nchunk;
 };
 
-template <bool CPLX>
+__device__ __forceinline__ int pair_index(int bi, int bj) { return bj * (bj + 1) / 2 + bi; }  // bi <= bj
+
+template <bool CPLX, int F>
 __global__ __launch_bounds__(256) void hoo_pair_kernel(HooPair a) {
-  constexpr int E = CPLX ? 2 : 1;
-  __shared__ double red[256][E];
-  const int pair = blockIdx.x / a.nchunk, chunk = blockIdx.x - pair * a.nchunk;
-  const int bi = pair / a.nb, bj = pair - bi * a.nb;
-  const int nfi = a.blk_nf[bi], nfj = a.blk_nf[bj], nit = nfi * nfj;
-  const int lanes = (int)blockDim.x / nit;
-  const int t = threadIdx.x, item = t % nit, lane = t / nit;
-  const int f = item / nfj, g = item - f * nfj;
+  constexpr int E = CPLX ? 2 : 1, lanes = 256 / F;
+  __shared__ double red[lanes * F * F * E];
+  // a chunk's pairs, which read the same cells' N^O, run together (on one XCD when the chunks divide evenly)
+  const int npair = a.nb * (a.nb + 1) / 2, xcd = a.nchunk % 8 ? 1 : 8;
+  const int slot = (int)blockIdx.x / xcd, pair = slot % npair, chunk = (int)blockIdx.x % xcd + slot / npair * xcd;
+  int bj = (int)((sqrtf(8.0f * pair + 1.0f) - 1.0f) * 0.5f);
+  while (bj * (bj + 1) / 2 > pair) --bj;
+  while ((bj + 1) * (bj + 2) / 2 <= pair) ++bj;
+  const int bi = pair - bj * (bj + 1) / 2;
+  const int t = threadIdx.x, lane = t / F, f = t - lane * F;
   const bool adapt = a.a_off != nullptr;
-  const int F = a.FMAX;
-  double sr = 0.0, si = 0.0;
+  double sr[F] = {}, si[F] = {};
   if (lane < lanes) {
     const int64_t pr = (int64_t)bi * a.nb + bj;
     const int64_t k0 = a.hp_ptr[pr], nk = a.hp_ptr[pr + 1] - k0;
     for (int64_t k = k0 + nk * chunk / a.nchunk; k < k0 + nk * (chunk + 1) / a.nchunk; ++k) {
       const int ci = a.hp_i[k], cj = a.hp_j[k];
-      int64_t np, p0 = 0, e = 0;
-      const double *pa, *pb;
+      int64_t np = a.nq;
+      const double *w, *v, *pa, *pb;
       if (adapt) {
         const int kc = a.cf_acell[ci];
-        p0 = a.a_off[kc];
+        const int64_t p0 = a.a_off[kc];
         np = a.a_off[kc + 1] - p0;
-        pa = a.phiA + (a.cf_aoff[ci] * F + f) * E;
-        pb = a.phiA + (a.cf_aoff[cj] * F + g) * E;
+        w = a.a_w + p0;
+        v = a.a_V + p0;
+        pa = a.phiA + a.cf_aoff[ci] * F * E;
+        pb = a.phiA + a.cf_aoff[cj] * F * E;
       } else {
-        e = a.cf_cell[ci];
-        np = a.nq;
-        pa = a.phi + ((int64_t)ci * a.nq * F + f) * E;
-        pb = a.phi + ((int64_t)cj * a.nq * F + g) * E;
+        const int64_t e = a.cf_cell[ci];
+        w = a.W + e * a.nq;
+        v = a.V + e * a.nq;
+        pa = a.phi + (int64_t)ci * a.nq * F * E;
+        pb = a.phi + (int64_t)cj * a.nq * F * E;
       }
       for (int64_t q = lane; q < np; q += lanes) {
-        const double wv = adapt ? a.a_w[p0 + q] * a.a_V[p0 + q] : a.W[e * a.nq + q] * a.V[e * a.nq + q];
-        const double ar = pa[q * F * E], ai = CPLX ? -pa[q * F * E + 1] : 0.0;
-        const double br = pb[q * F * E], bim = CPLX ? pb[q * F * E + 1] : 0.0;
-        const double xr = wv * ar, xi = wv * ai;
-        sr += xr * br - xi * bim;
-        if (CPLX) si += xr * bim + xi * br;
+        const double wv = w[q] * v[q];
+        const double* ai = pa + (q * F + f) * E;
+        const double xr = wv * ai[0], xi = CPLX ? -wv * ai[E - 1] : 0.0;
+#pragma unroll
+        for (int g = 0; g < F; ++g) {
+          const double* b = pb + (q * F + g) * E;
+          if constexpr (!CPLX) {
+            sr[g] += xr * b[0];
+          } else {
+            sr[g] += xr * b[0] - xi * b[1];
+            si[g] += xr * b[1] + xi * b[0];
+          }
+        }
       }
     }
-  }
-  red[t][0] = sr;
-  if (CPLX) red[t][E - 1] = si;
-  __syncthreads();
-  if (lane == 0) {
-    double tr = 0.0, ti = 0.0;
-    for (int l = 0; l < lanes; ++l) {
-      tr += red[l * nit + item][0];
-      if (CPLX) ti += red[l * nit + item][E - 1];
+#pragma unroll
+    for (int g = 0; g < F; ++g) {
+      red[((lane * F + f) * F + g) * E] = sr[g];
+      if (CPLX) red[((lane * F + f) * F + g) * E + E - 1] = si[g];
     }
-    double* o = a.part + (((int64_t)pair * a.nchunk + chunk) * a.FMAX * a.FMAX + item) * E;
-    o[0] = tr;
-    if (CPLX) o[1] = ti;
+  }
+  __syncthreads();
+  if (t < F * F * E) {
+    double s = 0.0;
+    for (int l = 0; l < lanes; ++l) s += red[l * F * F * E + t];
+    a.part[((int64_t)pair * a.nchunk + chunk) * F * F * E + t] = s;
   }
 }
 
@@ -958,13 +975,15 @@ __global__ __launch_bounds__(256) void hoo_sum_kernel(HooPair a) {
   const int i = t / a.nO, j = t - i * a.nO;
   const int bi = a.fn_blk[i], bj = a.fn_blk[j];
   const int f = i - a.blk_fn0[bi], g = j - a.blk_fn0[bj];
-  const int item = f * a.blk_nf[bj] + g;
-  const int64_t pair = (int64_t)bi * a.nb + bj;
+  const bool mirror = bi > bj;  // the pair (bj, bi) holds the conjugate transpose
+  const int item = mirror ? g * a.FMAX + f : f * a.FMAX + g;
+  const int64_t pair = mirror ? pair_index(bj, bi) : pair_index(bi, bj);
   double tr = a.Hoo_kin[(int64_t)t * E], ti = CPLX ? a.Hoo_kin[(int64_t)t * E + 1] : 0.0;
+#pragma unroll 8
   for (int c = 0; c < a.nchunk; ++c) {
     const double* p = a.part + ((pair * a.nchunk + c) * a.FMAX * a.FMAX + item) * E;
     tr += p[0];
-    if (CPLX) ti += p[1];
+    if (CPLX) ti += mirror ? -p[1] : p[1];
   }
   a.Hoo[(int64_t)t * E] = tr;
   a.Hoof[(int64_t)t * E] = (float)tr;
@@ -1459,13 +1478,22 @@ static int rebuild_potential_device(oefe_op op, hipStream_t s) {
     const int nb = (int)op->blocks.size();
     o.nO = op->n_enr; o.nb = nb; o.FMAX = op->FMAX; o.nq = op->nq; o.nchunk = op->hoo_nchunk;
     const unsigned g3 = (unsigned)(((int64_t)op->n_enr * op->n_enr + 255) / 256);
-    if (op->cplx) {
-      hipLaunchKernelGGL(hoo_pair_kernel<true>, dim3((unsigned)(nb * nb * op->hoo_nchunk)), dim3(256), 0, s, o);
-      hipLaunchKernelGGL(hoo_sum_kernel<true>, dim3(g3), dim3(256), 0, s, o);
-    } else {
-      hipLaunchKernelGGL(hoo_pair_kernel<false>, dim3((unsigned)(nb * nb * op->hoo_nchunk)), dim3(256), 0, s, o);
-      hipLaunchKernelGGL(hoo_sum_kernel<false>, dim3(g3), dim3(256), 0, s, o);
+    const dim3 g2((unsigned)((int64_t)nb * (nb + 1) / 2 * op->hoo_nchunk));
+    auto pairs = [&](auto kc, auto kr) { hipLaunchKernelGGL(op->cplx ? kc : kr, g2, dim3(256), 0, s, o); };
+    switch (op->FMAX) {
+      case 1: pairs(hoo_pair_kernel<true, 1>, hoo_pair_kernel<false, 1>); break;
+      case 2: pairs(hoo_pair_kernel<true, 2>, hoo_pair_kernel<false, 2>); break;
+      case 3: pairs(hoo_pair_kernel<true, 3>, hoo_pair_kernel<false, 3>); break;
+      case 4: pairs(hoo_pair_kernel<true, 4>, hoo_pair_kernel<false, 4>); break;
+      case 5: pairs(hoo_pair_kernel<true, 5>, hoo_pair_kernel<false, 5>); break;
+      case 6: pairs(hoo_pair_kernel<true, 6>, hoo_pair_kernel<false, 6>); break;
+      case 7: pairs(hoo_pair_kernel<true, 7>, hoo_pair_kernel<false, 7>); break;
+      default: pairs(hoo_pair_kernel<true, 8>, hoo_pair_kernel<false, 8>); break;
     }
+    if (op->cplx)
+      hipLaunchKernelGGL(hoo_sum_kernel<true>, dim3(g3), dim3(256), 0, s, o);
+    else
+      hipLaunchKernelGGL(hoo_sum_kernel<false>, dim3(g3), dim3(256), 0, s, o);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "potential rebuild");
