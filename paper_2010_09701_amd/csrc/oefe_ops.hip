@@ -1968,8 +1968,17 @@ __global__ void diag_step_kernel(const T* __restrict__ lam, const T* __restrict_
 // Density at the quadrature points for the potential gradient:
 //   dens[blk][e][q] = sum over the 64 real columns of this block of f_v psi_col(x_eq)^2,
 //   psi = B (m^-1/2 theta o x)|_e + sum_nu N^O_nu(x_eq) (S x^O)_nu.
-// Same plane layout as fe_cell_kernel (one cell x 64 real columns per workgroup).
+// One cell x 64 real columns per workgroup, the finite-element part in the plane layout of
+// fe_cell_kernel.  The enrichment part is a product (points x functions)(functions x columns) on the
+// matrix cores: with a thread per (column, points of one qx) every value N^O(x) was read from LDS for one
+// product, 5 waves x 25 points x 31 functions of them per cell and the larger part of the kernel.  A wave
+// takes row tiles w, w + P1, ... of 16 points and all column tiles, its accumulators start from the
+// finite-element values, N^O is read once from memory, and the sum over columns needs 4 shuffles of a point's
+// 16 lanes.  diamond8, 72 columns: 328 -> 163 us, of which the finite-element
+// part of the second, mostly empty block of columns is about a third.
 // ---------------------------------------------------------------------------
+constexpr int kFnList = 128;  // enrichment functions of a cell listed at a time
+
 template <typename T, int P1, bool CPLX>
 __global__ __launch_bounds__(64 * P1) void density_kernel(
     const T* __restrict__ X, int64_t ldx, int ncr, const double* __restrict__ fw, const T* __restrict__ zo,
@@ -1979,13 +1988,61 @@ __global__ __launch_bounds__(64 * P1) void density_kernel(
     double* __restrict__ dens, int64_t n_cells) {
   constexpr int NP = P1 * P1;
   constexpr int NQ = NP * P1;
-  __shared__ T lds[NQ][64];
+  __shared__ double smem[NQ * 64];
+  T(*lds)[64] = reinterpret_cast<T(*)[64]>(smem);
+  __shared__ struct {
+    int64_t phi;  // the function's entry of the cell's first point
+    int32_t fn;   // its row of Z^O, -1: none
+  } fnl[kFnList];
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int64_t e = blockIdx.x;
-  const int j = blockIdx.y * 64 + lane;
-  const bool valid = j < ncr;
-  const int cx = (int)(e % nc), cy = (int)((e / nc) % nc), cz = (int)(e / ((int64_t)nc * nc));
+  const int j = min((int)blockIdx.y * 64 + lane, ncr - 1);  // columns past ncr repeat the last and are left out below
+  const int cyz = (int)blockIdx.x / nc, cx = (int)blockIdx.x - cyz * nc, cz = cyz / nc, cy = cyz - cz * nc;
+  // the cell's enrichment functions in a flat list, kFnList at a time; a last k-step is filled up with Z = 0
+  constexpr int E = CPLX ? 2 : 1, NRT = (NQ + 15) / 16, NR = (NRT + P1 - 1) / P1, NCT = 4;
+  const int64_t k0 = cph_ptr[e], k1 = cph_ptr[e + 1];
+  const int nfn = (int)(k1 - k0) * FMAX, ln = lane & 15, lk = lane >> 4;
+  const int jb = blockIdx.y * 64, nct = min(NCT, (ncr - jb + 15) / 16);
+  auto nsteps = [&](int l0) { return (min(kFnList, nfn - l0) + 3) / 4; };
+  auto list = [&](int l0) {
+    for (int i = (int)threadIdx.x; i < 4 * nsteps(l0); i += 64 * P1) {
+      const int l = min(l0 + i, nfn - 1), b = l / FMAX, f = l - b * FMAX;
+      const int blk = cph_blk[k0 + b];
+      fnl[i].phi = (cph_off[k0 + b] * NQ * FMAX + f) * E;
+      fnl[i].fn = l0 + i < nfn && f < blk_nf[blk] ? blk_fn0[blk] + f : -1;
+    }
+  };
+  // a k-step's four functions: N^O at the row tiles' points, Z of the lane's columns (a complex pair also
+  // needs the swapped column: re: Re N Re z - Im N Im z, im: Re N Im z + Im N Re z)
+  struct KStep {
+    double pr[NR], pi[NR], z[NCT], zx[NCT];
+  };
+  auto load = [&](int st, KStep& k) {
+    const int64_t po = fnl[4 * st + lk].phi;
+    const int fn = fnl[4 * st + lk].fn;
+    const T* zp = zo + (int64_t)max(fn, 0) * ncr;
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) {
+      const int jc = min(jb + 16 * c + ln, ncr - 1);
+      k.z[c] = fn >= 0 ? (double)zp[jc] : 0.0;
+      if (CPLX) k.zx[c] = fn >= 0 ? ((jc & 1) ? (double)zp[jc ^ 1] : -(double)zp[jc ^ 1]) : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int q = min(16 * (w + r * P1) + ln, NQ - 1);
+      const double* pp = phi + po + (int64_t)q * FMAX * E;
+      k.pr[r] = pp[0];
+      k.pi[r] = CPLX ? pp[E - 1] : 0.0;
+    }
+  };
+  constexpr int D = CPLX ? 2 : 4;  // k-steps on their way: N^O comes from memory, and 10 waves are on a CU
+  KStep ring[D];
+  auto preload = [&](int l0) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) load(min(u, nsteps(l0) - 1), ring[u]);
+  };
+  if (nfn > 0) list(0);
   T v[NP], t[NP];
   {
     const int az = w;
@@ -2003,18 +2060,16 @@ __global__ __launch_bounds__(64 * P1) void density_kernel(
         const bool wx = ix >= n;
         if (wx) ix -= n;
         const int64_t g = ix + (int64_t)n * (iy + (int64_t)n * iz);
-        T val = 0;
-        if (valid) {
-          if constexpr (!CPLX) {
-            val = X[g * ldx + j];
-          } else {
-            const T* px = X + g * ldx + (j & ~1);
-            C2<T> z{px[0], px[1]};
-            if (wx) z = cmul(z, C2<T>{ph.re[0], ph.im[0]});
-            if (wy) z = cmul(z, C2<T>{ph.re[1], ph.im[1]});
-            if (wz) z = cmul(z, C2<T>{ph.re[2], ph.im[2]});
-            val = (j & 1) ? z.i : z.r;
-          }
+        T val;
+        if constexpr (!CPLX) {
+          val = X[g * ldx + j];
+        } else {
+          const T* px = X + g * ldx + (j & ~1);
+          C2<T> z{px[0], px[1]};
+          if (wx) z = cmul(z, C2<T>{ph.re[0], ph.im[0]});
+          if (wy) z = cmul(z, C2<T>{ph.re[1], ph.im[1]});
+          if (wz) z = cmul(z, C2<T>{ph.re[2], ph.im[2]});
+          val = (j & 1) ? z.i : z.r;
         }
         v[ay * P1 + ax] = cf.mscale * cf.om[ax] * cf.om[ay] * cf.om[az] * val;
       }
@@ -2039,12 +2094,14 @@ __global__ __launch_bounds__(64 * P1) void density_kernel(
       lds[(w * P1 + qy) * P1 + qx][lane] = s;
     }
   __syncthreads();
+  if (nfn > 0) preload(0);
 #pragma unroll
   for (int az = 0; az < P1; ++az)
 #pragma unroll
     for (int qy = 0; qy < P1; ++qy) t[az * P1 + qy] = lds[(az * P1 + qy) * P1 + w][lane];
-  const int qx = w;
-  double psi[NP];
+  // psi of the finite-element part at the points, float64, in the transpose's place
+  __syncthreads();
+  double(*psi)[64] = reinterpret_cast<double(*)[64]>(smem);
 #pragma unroll
   for (int qz = 0; qz < P1; ++qz)
 #pragma unroll
@@ -2052,108 +2109,65 @@ __global__ __launch_bounds__(64 * P1) void density_kernel(
       T s = 0;
 #pragma unroll
       for (int az = 0; az < P1; ++az) s += cf.B1[qz][az] * t[az * P1 + qy];
-      psi[qz * P1 + qy] = (double)s;
+      psi[(qz * P1 + qy) * P1 + w][lane] = (double)s;
     }
-  // enrichment part: the support blocks of the cell in turn; a block's values at the cell's points
-  // (all its functions) are staged in LDS by the whole workgroup, double-buffered: the next
-  // block's values and Z^O entries are loaded while this block's are summed; the sums run in the
-  // same order as one function after the other
-  {
-    constexpr int E = CPLX ? 2 : 1;
-    constexpr int kFn = 8;                                     // enrichment functions per atom at most
-    constexpr int kPer = (NQ * kFn * E + 64 * P1 - 1) / (64 * P1);  // staged values per thread at most
-    // two buffers of NQ FMAX E doubles: 2 x 125 x 8 x 2 x 8 B <= NQ x 64 x sizeof(T) for float and double
-    double* stg = reinterpret_cast<double*>(&lds[0][0]);
-    const int64_t k0 = cph_ptr[e], k1 = cph_ptr[e + 1];
-    const int cnt = NQ * FMAX * E, nth = 64 * P1, tid = (int)threadIdx.x;
-    double pre[kPer], zr[kFn], zi[kFn], zrn[kFn], zin[kFn];
-    int fn_next0 = 0, nf_next = 0;
-    auto fetch = [&](int64_t k) {  // block k's values into pre[], its Z^O entries into zrn / zin
-      const int b = cph_blk[k];
-      const int64_t off = cph_off[k];
+  double fv[NCT];
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int idx = tid + i * nth;
-        pre[i] = idx < cnt ? phi[off * cnt + idx] : 0.0;
+  for (int c = 0; c < NCT; ++c) {
+    const int jc = jb + 16 * c + ln;
+    fv[c] = jc < ncr ? fw[CPLX ? jc >> 1 : jc] : 0.0;
+  }
+  typedef Mfma<double>::V4 V4;
+  V4 acc[NR][NCT];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+#pragma unroll
+    for (int c = 0; c < NCT; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int q = 16 * (w + r * P1) + Mfma<double>::row(lane, v);
+        acc[r][c][v] = q < NQ ? psi[q][16 * c + ln] : 0.0;
       }
-      fn_next0 = blk_fn0[b];
-      nf_next = blk_nf[b];
+  for (int l0 = 0; l0 < nfn; l0 += kFnList) {
+    if (l0) {
+      __syncthreads();
+      list(l0);
+      __syncthreads();
+      preload(l0);
+    }
+    const int steps = nsteps(l0);
+    for (int st = 0; st < steps; st += D)
 #pragma unroll
-      for (int f = 0; f < kFn; ++f) {
-        zrn[f] = zin[f] = 0.0;
-        if (valid && f < nf_next) {
-          if constexpr (!CPLX) {
-            zrn[f] = (double)zo[(int64_t)(fn_next0 + f) * ncr + j];
-          } else {
-            zrn[f] = (double)zo[(int64_t)(fn_next0 + f) * ncr + (j & ~1)];
-            zin[f] = (double)zo[(int64_t)(fn_next0 + f) * ncr + (j & ~1) + 1];
+      for (int u = 0; u < D; ++u) {
+        if (st + u >= steps) break;
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          if (w + r * P1 >= NRT) break;
+#pragma unroll
+          for (int c = 0; c < NCT; ++c) {
+            if (c >= nct) break;
+            acc[r][c] = Mfma<double>::op(ring[u].pr[r], ring[u].z[c], acc[r][c]);
+            if (CPLX) acc[r][c] = Mfma<double>::op(ring[u].pi[r], ring[u].zx[c], acc[r][c]);
           }
         }
+        load(min(st + u + D, steps - 1), ring[u]);
       }
-    };
-    auto park = [&](double* buf) {
+  }
 #pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        const int idx = tid + i * nth;
-        if (idx < cnt) buf[idx] = pre[i];
-      }
-    };
-    if (k0 < k1) fetch(k0);
-    __syncthreads();  // the transpose is no longer read
-    if (k0 < k1) park(stg);
-    for (int64_t k = k0; k < k1; ++k) {
-      double* cur = stg + ((k - k0) & 1) * cnt;
-      const int nf = nf_next;
+  for (int r = 0; r < NR; ++r) {
+    if (w + r * P1 >= NRT) break;
 #pragma unroll
-      for (int f = 0; f < kFn; ++f) {
-        zr[f] = zrn[f];
-        zi[f] = zin[f];
-      }
-      __syncthreads();  // block k's values parked; the other buffer (block k - 1) no longer read
-      if (k + 1 < k1) fetch(k + 1);
-      if (valid) {
+    for (int v = 0; v < 4; ++v) {
+      double sum = 0.0;
 #pragma unroll
-        for (int f = 0; f < kFn; ++f) {
-          if (f >= nf) break;
-          if constexpr (!CPLX) {
-            const double z = zr[f];
+      for (int c = 0; c < NCT; ++c)
+        if (jb + 16 * c + ln < ncr) sum += fv[c] * acc[r][c][v] * acc[r][c][v];
 #pragma unroll
-            for (int qz = 0; qz < P1; ++qz)
-#pragma unroll
-              for (int qy = 0; qy < P1; ++qy) {
-                const int q = (qz * P1 + qy) * P1 + qx;
-                psi[qz * P1 + qy] += cur[q * FMAX + f] * z;
-              }
-          } else {
-#pragma unroll
-            for (int qz = 0; qz < P1; ++qz)
-#pragma unroll
-              for (int qy = 0; qy < P1; ++qy) {
-                const int q = (qz * P1 + qy) * P1 + qx;
-                const double pr = cur[2 * (q * FMAX + f)];
-                const double pi = cur[2 * (q * FMAX + f) + 1];
-                psi[qz * P1 + qy] += (j & 1) ? (pr * zi[f] + pi * zr[f]) : (pr * zr[f] - pi * zi[f]);
-              }
-          }
-        }
-      }
-      if (k + 1 < k1) park(stg + ((k + 1 - k0) & 1) * cnt);
+      for (int o = 8; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 16);
+      const int q = 16 * (w + r * P1) + Mfma<double>::row(lane, v);
+      if (ln == 0 && q < NQ) dens[((int64_t)blockIdx.y * n_cells + e) * NQ + q] = sum;
     }
-  }
-  const double fv = valid ? fw[CPLX ? (j >> 1) : j] : 0.0;
-#pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    double s = valid ? fv * psi[k] * psi[k] : 0.0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    psi[k] = s;
-  }
-  if (lane == 0) {
-    double* out = dens + ((int64_t)blockIdx.y * n_cells + e) * NQ;
-#pragma unroll
-    for (int qz = 0; qz < P1; ++qz)
-#pragma unroll
-      for (int qy = 0; qy < P1; ++qy) out[(qz * P1 + qy) * P1 + qx] = psi[qz * P1 + qy];
   }
 }
 
