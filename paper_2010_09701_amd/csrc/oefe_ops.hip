@@ -442,8 +442,205 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The three products of small_gemm modes 1, 2 and 3 in one launch: every product is
+// (n x n) times (n x columns), so one workgroup per block of kChainCols columns computes
+//   W' = (sum of the folded tile partials) + H^oo Z^O,
+//   out^O = alpha (S W' - c x^O) - beta prev^O,
+//   Z^O of the next step = S out^O (when next),
+// with S, H^oo and the block's Z^O, W' and out^O in LDS (1024 threads: one output of a phase
+// per thread for n kChainCols <= 1024).  Sums run in the same order as in
+// small_gemm (chunk partials first, then the products in k order); the chunk partials are
+// loaded in batches of 8.
+//
+// Blocks of kChainColsCell columns and 256 threads run it as the first blocks of the cell launch, which
+// it does not depend on, where a step is short (chain_in_cell): the same sums in the same order.
+constexpr int kChainCols = 16;
+
+constexpr int kChainColsCell = 4;
+constexpr int64_t kChainInCellElems = (int64_t)1 << 23;  // real elements of the step's blocks (chain_in_cell)
+
+template <typename T, bool CPLX>
+constexpr size_t enr_chain_lds_bytes(int n, int cols = kChainCols) {
+  return (2 * (size_t)n * n + 3 * (size_t)n * cols) * (CPLX ? 2 : 1) * sizeof(T);
+}
+
+// fn_pptr null: the partials are folded (part2); else every function's are folded here
+struct ChainArgs {
+  int64_t N;
+  int n, next;
+  const int32_t *fn_pptr, *fn_poff;
+  int nblk;  // leading blocks of a cell launch that run the chain, 0: none
+};
+
+template <typename T, bool CPLX, int TC>
+__device__ __forceinline__ void enr_chain(const KBatch<T>& kb, const ChainArgs& ca, int block, unsigned char* chain_raw) {
+  constexpr int E = CPLX ? 2 : 1;
+  const int64_t N = ca.N;
+  const int n = ca.n, next = ca.next;
+  const int32_t* __restrict__ fn_pptr = ca.fn_pptr;
+  const int32_t* __restrict__ fn_poff = ca.fn_poff;
+  T* Ss = reinterpret_cast<T*>(chain_raw);  // [n][n] S
+  T* Hs = Ss + (size_t)n * n * E;           // [n][n] H^oo
+  T* Zs = Hs + (size_t)n * n * E;           // [n][TC] Z^O of this step
+  T* Ws = Zs + (size_t)n * TC * E;          // [n][TC] W'
+  T* Os = Ws + (size_t)n * TC * E;          // [n][TC] out^O
+  const KP<T>& P = kb.k[blockIdx.z];
+  const int m = P.nv, ncr = P.ncr;
+  const int j0 = block * TC;
+  if (j0 >= m) return;
+  const int tid = threadIdx.x, nth = blockDim.x;
+  for (int t = tid; t < n * n * E; t += nth) {
+    Ss[t] = P.S[t];
+    Hs[t] = P.Hoo[t];
+  }
+  for (int t = tid; t < n * TC; t += nth) {
+    const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
+#pragma unroll
+    for (int e = 0; e < E; ++e) Zs[(size_t)t * E + e] = P.zo[(int64_t)i * ncr + (int64_t)j * E + e];
+  }
+  __syncthreads();
+  // sum_k A[i][k] B[k][jl] over LDS tiles, in k order
+  auto dot = [&](const T* A, const T* B, int i, int jl, T& sr, T& si) {
+    sr = 0;
+    si = 0;
+#pragma unroll 8
+    for (int k = 0; k < n; ++k) {
+      const T* a = A + ((size_t)i * n + k) * E;
+      const T* b = B + ((size_t)k * TC + jl) * E;
+      if constexpr (!CPLX) {
+        sr += a[0] * b[0];
+      } else {
+        const C2<T> q = cmul(C2<T>{a[0], a[1]}, C2<T>{b[0], b[1]});
+        sr += q.r;
+        si += q.i;
+      }
+    }
+  };
+  // W'
+  if (fn_pptr) {
+    // every function has at most kReduceChunk partials: folded here, in the order of enr_reduce1_kernel
+    for (int t = tid; t < n * TC; t += nth) {
+      const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
+      const int e0 = fn_pptr[i], cnt = fn_pptr[i + 1] - e0;
+      T wr[4], wi[4];
+#pragma unroll
+      for (int grp = 0; grp < 4; ++grp) {
+        T r[2] = {0, 0}, q[2] = {0, 0};  // even and odd entries of the group
+        for (int k = 0; grp + 4 * k < cnt; ++k) {
+          const T* v = P.part + (int64_t)fn_poff[e0 + grp + 4 * k] * ncr + (int64_t)j * E;
+          if (k & 1) {
+            r[1] += v[0];
+            if (CPLX) q[1] += v[1];
+          } else {
+            r[0] += v[0];
+            if (CPLX) q[0] += v[1];
+          }
+        }
+        wr[grp] = r[0] + r[1];
+        wi[grp] = q[0] + q[1];
+      }
+      T sr, si;
+      dot(Hs, Zs, i, jl, sr, si);
+      Ws[(size_t)t * E] = ((wr[0] + wr[1]) + (wr[2] + wr[3])) + sr;
+      if (CPLX) Ws[(size_t)t * E + 1] = ((wi[0] + wi[1]) + (wi[2] + wi[3])) + si;
+    }
+  } else if (m == 1) {
+    // one column: the TC threads of a row, which would all compute the same entry, split its
+    // chunks (thread jl adds chunks jl, jl + TC, ... in order) into Os, then add them in order
+    for (int t = tid; t < n * TC; t += nth) {
+      const int i = t / TC, jl = t - i * TC;
+      const T* p2 = P.part2 + (int64_t)i * P.nch * ncr;
+      T wr = 0, wi = 0;
+      for (int ch = jl; ch < P.nch; ch += TC) {
+        wr += p2[(int64_t)ch * ncr];
+        if (CPLX) wi += p2[(int64_t)ch * ncr + 1];
+      }
+      Os[(size_t)t * E] = wr;
+      if (CPLX) Os[(size_t)t * E + 1] = wi;
+    }
+    __syncthreads();
+    for (int t = tid; t < n * TC; t += nth) {
+      const int i = t / TC, jl = t - i * TC;
+      T wr = 0, wi = 0;
+      for (int q = 0; q < TC; ++q) {
+        wr += Os[((size_t)i * TC + q) * E];
+        if (CPLX) wi += Os[((size_t)i * TC + q) * E + 1];
+      }
+      T sr, si;
+      dot(Hs, Zs, i, jl, sr, si);
+      Ws[(size_t)t * E] = wr + sr;
+      if (CPLX) Ws[(size_t)t * E + 1] = wi + si;
+    }
+  } else {
+  for (int t = tid; t < n * TC; t += nth) {
+    const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
+    const T* p2 = P.part2 + (int64_t)i * P.nch * ncr + (int64_t)j * E;
+    T wr = 0, wi = 0;
+    int ch = 0;
+    for (; ch + 8 <= P.nch; ch += 8) {
+      T vr[8], vi[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        vr[q] = p2[(int64_t)(ch + q) * ncr];
+        vi[q] = CPLX ? p2[(int64_t)(ch + q) * ncr + 1] : T(0);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        wr += vr[q];
+        if (CPLX) wi += vi[q];
+      }
+    }
+    for (; ch < P.nch; ++ch) {
+      wr += p2[(int64_t)ch * ncr];
+      if (CPLX) wi += p2[(int64_t)ch * ncr + 1];
+    }
+    T sr, si;
+    dot(Hs, Zs, i, jl, sr, si);
+    Ws[(size_t)t * E] = wr + sr;
+    if (CPLX) Ws[(size_t)t * E + 1] = wi + si;
+  }
+  }
+  __syncthreads();
+  // out^O
+  for (int t = tid; t < n * TC; t += nth) {
+    const int i = t / TC, jl = t - i * TC, j = j0 + jl;
+    T sr, si;
+    dot(Ss, Ws, i, jl, sr, si);
+    const int64_t ox = (N + i) * P.ldx + (int64_t)min(j, m - 1) * E, oo = (N + i) * P.ldo + (int64_t)min(j, m - 1) * E;
+    T alpha, cst, beta;
+    step_scalars(P, alpha, cst, beta);
+    T r = alpha * (sr - cst * P.x[ox]);
+    if (beta != T(0)) r -= beta * P.prev[oo];
+    T r2 = 0;
+    if (CPLX) {
+      r2 = alpha * (si - cst * P.x[ox + 1]);
+      if (beta != T(0)) r2 -= beta * P.prev[oo + 1];
+    }
+    Os[(size_t)t * E] = r;
+    if (CPLX) Os[(size_t)t * E + 1] = r2;
+    if (j < m) {
+      P.out[oo] = r;
+      if (CPLX) P.out[oo + 1] = r2;
+    }
+  }
+  if (!next) return;
+  __syncthreads();
+  // Z^O of the next step
+  for (int t = tid; t < n * TC; t += nth) {
+    const int i = t / TC, jl = t - i * TC, j = j0 + jl;
+    T sr, si;
+    dot(Ss, Os, i, jl, sr, si);
+    if (j < m) {
+      P.zn[(int64_t)i * ncr + (int64_t)j * E] = sr;
+      if (CPLX) P.zn[(int64_t)i * ncr + (int64_t)j * E + 1] = si;
+    }
+  }
+}
+
 template <int P1>
 constexpr int lanes_cw() { return (64 / P1) & ~1; }
+template <typename T, int P1>
+constexpr size_t cell_lanes_lds_bytes() { return 4 * (P1 * P1 * P1 * lanes_cw<P1>() + 128) * sizeof(T); }
 
 // UF: the periodic-function k-point form's first-derivative term -i k . int N grad N is added
 // (complex columns only): k . grad u at the Gauss points (derivatives of the interpolant of the
@@ -452,7 +649,7 @@ constexpr int lanes_cw() { return (64 / P1) & ~1; }
 // the backward passes project.
 template <typename T, int P1, bool CPLX, bool UF = false>
 __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, CellCoef<T> cf, int nc, int p, int n,
-                                                            int64_t n_cells, int nch) {
+                                                            int64_t n_cells, int nch, ChainArgs ca) {
   static_assert(!UF || CPLX, "the first-derivative term acts on complex columns");
   constexpr int NP = P1 * P1;
   constexpr int CWc = lanes_cw<P1>();
@@ -462,11 +659,17 @@ __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, Cel
   // launch order: the column chunks of a group of 4 cells are consecutive in L, and each
   // XCD (workgroups bk = x mod 8) takes a contiguous range of L, so that the chunks reading
   // the same node rows, and neighbouring cells, share one L2
-  const int nbk = gridDim.x, bk = blockIdx.x, nb8 = nbk & ~7;
+  extern __shared__ __align__(16) unsigned char cell_raw[];
+  if ((int)blockIdx.x < ca.nblk) {  // the enrichment chain of this step
+    enr_chain<T, CPLX, kChainColsCell>(kb, ca, (int)blockIdx.x, cell_raw);
+    return;
+  }
+  const int nbk = (int)gridDim.x - ca.nblk, bk = (int)blockIdx.x - ca.nblk, nb8 = nbk & ~7;
   const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
   const int chunk = L % nch, cgrp = L / nch;
-  __shared__ T lds_all[4][NP * P1 * CWc];
-  __shared__ T wv_all[4][128];  // W V of the wave's cell at its quadrature points
+  T(*lds_all)[NP * P1 * CWc] = reinterpret_cast<T(*)[NP * P1 * CWc]>(cell_raw);
+  // W V of the wave's cell at its quadrature points
+  T(*wv_all)[128] = reinterpret_cast<T(*)[128]>(cell_raw + 4 * sizeof(lds_all[0]));
   const KP<T>& P = kb.k[blockIdx.z];
   const int ncr = P.ncr;
   if (chunk * CWc >= ncr) return;  // column block beyond this operator's width
@@ -1768,184 +1971,10 @@ __global__ __launch_bounds__(256) void small_gemm_kernel(KBatch<T> kb, int mode,
   }
 }
 
-// The three products of small_gemm modes 1, 2 and 3 in one launch: every product is
-// (n x n) times (n x columns), so one workgroup per block of kChainCols columns computes
-//   W' = (sum of the folded tile partials) + H^oo Z^O,
-//   out^O = alpha (S W' - c x^O) - beta prev^O,
-//   Z^O of the next step = S out^O (when next),
-// with S, H^oo and the block's Z^O, W' and out^O in LDS (1024 threads: one output of a phase
-// per thread for n kChainCols <= 1024).  Sums run in the same order as in
-// small_gemm (chunk partials first, then the products in k order); the chunk partials are
-// loaded in batches of 8.
-constexpr int kChainCols = 16;
-
 template <typename T, bool CPLX>
-constexpr size_t enr_chain_lds_bytes(int n) {
-  return (2 * (size_t)n * n + 3 * (size_t)n * kChainCols) * (CPLX ? 2 : 1) * sizeof(T);
-}
-
-template <typename T, bool CPLX>
-__global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, int64_t N, int n, int next,
-                                                         const int32_t* __restrict__ fn_pptr,
-                                                         const int32_t* __restrict__ fn_poff) {
-  constexpr int E = CPLX ? 2 : 1, TC = kChainCols;
-  extern __shared__ unsigned char chain_raw[];
-  T* Ss = reinterpret_cast<T*>(chain_raw);  // [n][n] S
-  T* Hs = Ss + (size_t)n * n * E;           // [n][n] H^oo
-  T* Zs = Hs + (size_t)n * n * E;           // [n][TC] Z^O of this step
-  T* Ws = Zs + (size_t)n * TC * E;          // [n][TC] W'
-  T* Os = Ws + (size_t)n * TC * E;          // [n][TC] out^O
-  const KP<T>& P = kb.k[blockIdx.z];
-  const int m = P.nv, ncr = P.ncr;
-  const int j0 = blockIdx.x * TC;
-  if (j0 >= m) return;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  for (int t = tid; t < n * n * E; t += nth) {
-    Ss[t] = P.S[t];
-    Hs[t] = P.Hoo[t];
-  }
-  for (int t = tid; t < n * TC; t += nth) {
-    const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
-#pragma unroll
-    for (int e = 0; e < E; ++e) Zs[(size_t)t * E + e] = P.zo[(int64_t)i * ncr + (int64_t)j * E + e];
-  }
-  __syncthreads();
-  // sum_k A[i][k] B[k][jl] over LDS tiles, in k order
-  auto dot = [&](const T* A, const T* B, int i, int jl, T& sr, T& si) {
-    sr = 0;
-    si = 0;
-#pragma unroll 8
-    for (int k = 0; k < n; ++k) {
-      const T* a = A + ((size_t)i * n + k) * E;
-      const T* b = B + ((size_t)k * TC + jl) * E;
-      if constexpr (!CPLX) {
-        sr += a[0] * b[0];
-      } else {
-        const C2<T> q = cmul(C2<T>{a[0], a[1]}, C2<T>{b[0], b[1]});
-        sr += q.r;
-        si += q.i;
-      }
-    }
-  };
-  // W'
-  if (fn_pptr) {
-    // every function has at most kReduceChunk partials: folded here, in the order of enr_reduce1_kernel
-    for (int t = tid; t < n * TC; t += nth) {
-      const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
-      const int e0 = fn_pptr[i], cnt = fn_pptr[i + 1] - e0;
-      T wr[4], wi[4];
-#pragma unroll
-      for (int grp = 0; grp < 4; ++grp) {
-        T r[2] = {0, 0}, q[2] = {0, 0};  // even and odd entries of the group
-        for (int k = 0; grp + 4 * k < cnt; ++k) {
-          const T* v = P.part + (int64_t)fn_poff[e0 + grp + 4 * k] * ncr + (int64_t)j * E;
-          if (k & 1) {
-            r[1] += v[0];
-            if (CPLX) q[1] += v[1];
-          } else {
-            r[0] += v[0];
-            if (CPLX) q[0] += v[1];
-          }
-        }
-        wr[grp] = r[0] + r[1];
-        wi[grp] = q[0] + q[1];
-      }
-      T sr, si;
-      dot(Hs, Zs, i, jl, sr, si);
-      Ws[(size_t)t * E] = ((wr[0] + wr[1]) + (wr[2] + wr[3])) + sr;
-      if (CPLX) Ws[(size_t)t * E + 1] = ((wi[0] + wi[1]) + (wi[2] + wi[3])) + si;
-    }
-  } else if (m == 1) {
-    // one column: the TC threads of a row, which would all compute the same entry, split its
-    // chunks (thread jl adds chunks jl, jl + TC, ... in order) into Os, then add them in order
-    for (int t = tid; t < n * TC; t += nth) {
-      const int i = t / TC, jl = t - i * TC;
-      const T* p2 = P.part2 + (int64_t)i * P.nch * ncr;
-      T wr = 0, wi = 0;
-      for (int ch = jl; ch < P.nch; ch += TC) {
-        wr += p2[(int64_t)ch * ncr];
-        if (CPLX) wi += p2[(int64_t)ch * ncr + 1];
-      }
-      Os[(size_t)t * E] = wr;
-      if (CPLX) Os[(size_t)t * E + 1] = wi;
-    }
-    __syncthreads();
-    for (int t = tid; t < n * TC; t += nth) {
-      const int i = t / TC, jl = t - i * TC;
-      T wr = 0, wi = 0;
-      for (int q = 0; q < TC; ++q) {
-        wr += Os[((size_t)i * TC + q) * E];
-        if (CPLX) wi += Os[((size_t)i * TC + q) * E + 1];
-      }
-      T sr, si;
-      dot(Hs, Zs, i, jl, sr, si);
-      Ws[(size_t)t * E] = wr + sr;
-      if (CPLX) Ws[(size_t)t * E + 1] = wi + si;
-    }
-  } else {
-  for (int t = tid; t < n * TC; t += nth) {
-    const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
-    const T* p2 = P.part2 + (int64_t)i * P.nch * ncr + (int64_t)j * E;
-    T wr = 0, wi = 0;
-    int ch = 0;
-    for (; ch + 8 <= P.nch; ch += 8) {
-      T vr[8], vi[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        vr[q] = p2[(int64_t)(ch + q) * ncr];
-        vi[q] = CPLX ? p2[(int64_t)(ch + q) * ncr + 1] : T(0);
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        wr += vr[q];
-        if (CPLX) wi += vi[q];
-      }
-    }
-    for (; ch < P.nch; ++ch) {
-      wr += p2[(int64_t)ch * ncr];
-      if (CPLX) wi += p2[(int64_t)ch * ncr + 1];
-    }
-    T sr, si;
-    dot(Hs, Zs, i, jl, sr, si);
-    Ws[(size_t)t * E] = wr + sr;
-    if (CPLX) Ws[(size_t)t * E + 1] = wi + si;
-  }
-  }
-  __syncthreads();
-  // out^O
-  for (int t = tid; t < n * TC; t += nth) {
-    const int i = t / TC, jl = t - i * TC, j = j0 + jl;
-    T sr, si;
-    dot(Ss, Ws, i, jl, sr, si);
-    const int64_t ox = (N + i) * P.ldx + (int64_t)min(j, m - 1) * E, oo = (N + i) * P.ldo + (int64_t)min(j, m - 1) * E;
-    T alpha, cst, beta;
-    step_scalars(P, alpha, cst, beta);
-    T r = alpha * (sr - cst * P.x[ox]);
-    if (beta != T(0)) r -= beta * P.prev[oo];
-    T r2 = 0;
-    if (CPLX) {
-      r2 = alpha * (si - cst * P.x[ox + 1]);
-      if (beta != T(0)) r2 -= beta * P.prev[oo + 1];
-    }
-    Os[(size_t)t * E] = r;
-    if (CPLX) Os[(size_t)t * E + 1] = r2;
-    if (j < m) {
-      P.out[oo] = r;
-      if (CPLX) P.out[oo + 1] = r2;
-    }
-  }
-  if (!next) return;
-  __syncthreads();
-  // Z^O of the next step
-  for (int t = tid; t < n * TC; t += nth) {
-    const int i = t / TC, jl = t - i * TC, j = j0 + jl;
-    T sr, si;
-    dot(Ss, Os, i, jl, sr, si);
-    if (j < m) {
-      P.zn[(int64_t)i * ncr + (int64_t)j * E] = sr;
-      if (CPLX) P.zn[(int64_t)i * ncr + (int64_t)j * E + 1] = si;
-    }
-  }
+__global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, ChainArgs ca) {
+  extern __shared__ __align__(16) unsigned char chain_raw[];
+  enr_chain<T, CPLX, kChainCols>(kb, ca, (int)blockIdx.x, chain_raw);
 }
 
 // diagonal test operator: out = alpha (lambda x - c x) - beta prev
@@ -2236,19 +2265,21 @@ void launch_cell_p(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, int cw
 }
 
 template <typename T, int P1, bool CPLX>
-void launch_cell_lanes(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, hipStream_t s) {
+void launch_cell_lanes(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, hipStream_t s, const ChainArgs& ca) {
   constexpr int CWc = lanes_cw<P1>();
   const int nch = (int)cdiv(max_ncr, CWc);
-  dim3 grid((unsigned)(cdiv(op->n_cells, 4) * nch), 1, (unsigned)kb.nk);
+  dim3 grid((unsigned)(cdiv(op->n_cells, 4) * nch + ca.nblk), 1, (unsigned)kb.nk);
+  const size_t lds = std::max(cell_lanes_lds_bytes<T, P1>(),
+                              ca.nblk ? enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell) : (size_t)0);
   if constexpr (CPLX) {
     if (op->uform) {  // the operators of a batch share the form (checked by the batched entry points)
-      hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, true, true>), grid, dim3(256), 0, s, kb, coef<T>(op), op->nc,
-                         op->p, op->n, op->n_cells, nch);
+      hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, true, true>), grid, dim3(256), lds, s, kb, coef<T>(op), op->nc,
+                         op->p, op->n, op->n_cells, nch, ca);
       return;
     }
   }
-  hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, CPLX>), grid, dim3(256), 0, s, kb, coef<T>(op), op->nc, op->p, op->n,
-                     op->n_cells, nch);
+  hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, CPLX>), grid, dim3(256), lds, s, kb, coef<T>(op), op->nc, op->p, op->n,
+                     op->n_cells, nch, ca);
 }
 
 // The planes-in-lanes kernel forms row offsets within a z-plane of X and of the node-slot
@@ -2263,6 +2294,25 @@ bool lanes_offsets_fit(const oefe_op_s* op, const KBatch<T>& kb) {
   return true;
 }
 
+// Whether a recurrence's step runs its enrichment chain as the first blocks of the cell launch, in
+// stream order, instead of on the side stream beside the cell and node stages: two launches a step (three
+// with the fold of many partials) against three or four and four event calls.  Microseconds a step, side
+// stream -> in the cell launch: one atom, 4 k elements 32.3 -> 18.8, 0.8 M 34.4 -> 27.8; eight atoms
+// 0.34 M 36.9 -> 30.2 (float32 42.5 -> 25.1), 1.6 M 47.1 -> 42.9, 4.1 M 87.0 -> 82.1, 8.0 M 169.2 -> 168.0
+// (float32 98.7 -> 96.6); four k-points of 17 M elements each 1703 -> 1726 and 1880 -> 1953
+// (periodic-function form): there the fold, not the waits, is what the side stream hides.
+template <typename T, bool CPLX>
+bool chain_in_cell(const oefe_op_s* op, const KBatch<T>& kb, bool bf16) {
+  if (bf16 || op->n_enr < 1 || (op->tune_cw != 0 && !op->uform) || !lanes_offsets_fit(op, kb)) return false;
+  if (enr_chain_lds_bytes<T, CPLX>(op->n_enr, kChainColsCell) > 64 * 1024) return false;
+  int64_t elems = 0;
+  for (int q = 0; q < kb.nk; ++q) {
+    if (kb.k[q].nv < 2) return false;  // one column folds its partials in another order
+    elems += op->N * kb.k[q].ncr;
+  }
+  return elems <= kChainInCellElems;
+}
+
 // cw = 0: planes-in-lanes kernel; 8, 16, 32, 64: plane-per-wave kernel with cw columns per cell
 template <typename T, int P1>
 void launch_cell_cells(const oefe_op_s* op, const KBatch<T>& kb, hipStream_t s) {
@@ -2272,7 +2322,7 @@ void launch_cell_cells(const oefe_op_s* op, const KBatch<T>& kb, hipStream_t s) 
 }
 
 template <typename T, bool CPLX>
-void launch_cell(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, int cw, hipStream_t s) {
+void launch_cell(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, int cw, hipStream_t s, const ChainArgs& ca) {
   if constexpr (!CPLX) {
     if (max_ncr == 1) {  // one real column: cells in the lanes, whatever the tuned shape
       switch (op->P1) {
@@ -2292,9 +2342,9 @@ void launch_cell(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, int cw, 
   }
   if (cw == 0) {
     switch (op->P1) {
-      case 3: launch_cell_lanes<T, 3, CPLX>(op, kb, max_ncr, s); break;
-      case 4: launch_cell_lanes<T, 4, CPLX>(op, kb, max_ncr, s); break;
-      default: launch_cell_lanes<T, 5, CPLX>(op, kb, max_ncr, s); break;
+      case 3: launch_cell_lanes<T, 3, CPLX>(op, kb, max_ncr, s, ca); break;
+      case 4: launch_cell_lanes<T, 4, CPLX>(op, kb, max_ncr, s, ca); break;
+      default: launch_cell_lanes<T, 5, CPLX>(op, kb, max_ncr, s, ca); break;
     }
     return;
   }
@@ -2414,6 +2464,7 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
       op->timer_events.emplace_back(ev0, ev1);
     }
   };
+  ChainArgs ca{};
   auto cell_stage = [&] {
     timed(OEFE_TIMER_CELL, s, [&] {
       if constexpr (std::is_same<T, float>::value && !CPLX) {
@@ -2422,7 +2473,7 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
           return;
         }
       }
-      launch_cell<T, CPLX>(op, kb, max_ncr, op->tune_cw, s);
+      launch_cell<T, CPLX>(op, kb, max_ncr, op->tune_cw, s, ca);
     });
   };
   const dim3 gg((unsigned)cdiv(max_nv, 16), (unsigned)cdiv(nO, 16), nk);
@@ -2442,9 +2493,9 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
   };
   auto chain = [&](hipStream_t se) {
     if (one_chain) {
+      const ChainArgs c{op->N, nO, (ovl && !ov->last) ? 1 : 0, direct ? op->d.fn_pptr : nullptr, op->d.fn_poff, 0};
       hipLaunchKernelGGL((enr_chain_kernel<T, CPLX>), dim3((unsigned)cdiv(max_nv, kChainCols), 1, nk), dim3(1024), clds,
-                         se, kb, op->N, nO, (ovl && !ov->last) ? 1 : 0, direct ? op->d.fn_pptr : nullptr,
-                         op->d.fn_poff);
+                         se, kb, c);
     } else {
       hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 1, op->N, nO);
       hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, se, kb, 2, op->N, nO);
@@ -2457,7 +2508,7 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
   const bool col1 = !CPLX && !ovl && max_ncr == 1 && op->tile_fpmax <= kCol1MaxFunctions;
   // A recurrence forms each step's partials Ht_t^* X with the X that the previous step wrote, while it
   // is in registers; its first step, from X itself, before the node stage.
-  const bool ahead = ovl;
+  const bool ahead = ovl, inl = ahead && one_chain && chain_in_cell<T, CPLX>(op, kb, bf16);
   int rc = OEFE_OK;
   if (nO > 0 && (!ovl || ov->first)) {
     hipLaunchKernelGGL((small_gemm_kernel<T, CPLX>), gg, dim3(256), 0, s, kb, 0, op->N, nO);
@@ -2465,19 +2516,24 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
       rc = launch_node<T, CPLX>(op, kb, max_ncr, NodeRun::part, s);
       if (rc) return rc;
       fold(s);
-      (void)hipEventRecord(ov->ev_node, s);
-      (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
+      if (!inl) {
+        (void)hipEventRecord(ov->ev_node, s);
+        (void)hipStreamWaitEvent(ov->side, ov->ev_node, 0);
+      }
     }
   }
+  if (inl)
+    ca = ChainArgs{op->N, nO, ov->last ? 0 : 1, direct ? op->d.fn_pptr : nullptr, op->d.fn_poff,
+                   (int)cdiv(cdiv(max_nv, kChainColsCell), 8) * 8};  // (whole rounds of the XCDs)
   // The chain of this step (folded partials, Z^O and enrichment rows are there) beside its cell and
   // node stages: the next step's Z^O goes to a buffer of its own
-  if (nO > 0 && ahead) {
+  if (nO > 0 && ahead && !inl) {
     chain(ov->side);
     if (direct) (void)hipEventRecord(ov->ev_zo, ov->side);  // the partials are read
   }
   cell_stage();
   // this step's Z^O is there and its partials are folded
-  if (ovl && nO > 0 && (direct || !ov->first)) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);
+  if (ovl && nO > 0 && !inl && (direct || !ov->first)) (void)hipStreamWaitEvent(s, ov->ev_zo, 0);
   if (col1) {
     if constexpr (!CPLX) {
       const int ntiles = tile_count(op->n, op->tile_mode);
@@ -2494,7 +2550,9 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
     timed(kind, s, [&] { rc = launch_node<T, CPLX>(op, kb, max_ncr, run, s); });
     if (rc) return rc;
   }
-  if (nO > 0 && ahead) {
+  if (inl) {
+    if (!ov->last) fold(s);
+  } else if (nO > 0 && ahead) {
     // the fold of the next step's partials beside its cell stage
     if (!ov->last) {
       (void)hipEventRecord(ov->ev_node, s);

@@ -51,3 +51,22 @@ def test_node_stage_column_groups(name, dt):
         assert _colrel(oefe.ham_apply(gop, Xd).cpu().numpy(), Y[:, :nv]) < tol, nv
         oefe.chebyshev_filter(gop, Xd, 2, a, b, a0)
         assert _colrel(Xd.cpu().numpy(), F[:, :nv]) < tol, nv
+
+
+@pytest.mark.parametrize("dt,nv,sub", [("float64", 181, (2, 3, 4, 5, 64)), ("float32", 181, (2, 33)),
+                                       ("complex128", 92, (2, 5, 17)), ("complex64", 92, (2, 33))])
+def test_recurrence_enrichment_chain_placement(dt, nv, sub):
+    """A recurrence whose blocks hold more than 2^23 real elements runs the enrichment chain on the side
+    stream, a smaller one in the cell launch: the same sums in the same order, so the columns of a wide
+    block and of narrow ones are equal to the bit."""
+    import torch
+    from paper_2010_09701_amd import oefe
+    sysm = wl.diamond8(nc=9, p=4)
+    op = oefe.Operator(sysm.with_k(K) if dt.startswith("complex") else sysm)
+    assert op.n_tot * nv * (2 if dt.startswith("complex") else 1) > 1 << 23
+    X = torch.from_numpy(wl.start_block(op.n_tot, nv, 5, complex_=dt.startswith("complex"))).to(getattr(torch, dt)).cuda()
+    a0, b = oefe.lanczos_bounds(op, torch.from_numpy(wl.lanczos_start(op.n_tot, 2)).cuda(), 10)[:2]
+    wide = oefe.chebyshev_filter(op, X.clone(), 5, 0.5 * (a0 + b), b, a0)
+    for w in sub:
+        narrow = oefe.chebyshev_filter(op, X[:, :w].contiguous(), 5, 0.5 * (a0 + b), b, a0)
+        assert torch.equal(narrow, wide[:, :w]), w
