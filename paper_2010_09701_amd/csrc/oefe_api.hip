@@ -2411,8 +2411,8 @@ __global__ void pois_start_kernel(const double* __restrict__ v, double* __restri
 }
 
 // x += alpha p, r -= alpha q with alpha = rr / pq (0 when pq <= 0), and the chunk partials of
-// r_new . r_new in the chunking and summation order of the one-column dot product
-// (dot1_chunk_count, dot1_final): the step and the dot in one pass over r, the dot's bits
+// r_new . r_new, a thread's rows 1024 apart, then a fixed butterfly per wave and the 16 wave sums in order
+constexpr int kPoisChunks = 256;
 __global__ __launch_bounds__(1024) void pois_step_rr_kernel(double* __restrict__ x, double* __restrict__ r,
                                                             const double* __restrict__ pv, const double* __restrict__ q,
                                                             const double* __restrict__ rr, const double* __restrict__ pq,
@@ -2424,7 +2424,7 @@ __global__ __launch_bounds__(1024) void pois_step_rr_kernel(double* __restrict__
     x[g] += al * pv[g];
     const double rn = r[g] - al * q[g];
     r[g] = rn;
-    return rn * rn + 0.0;  // the dot kernel's term, written the same way
+    return rn * rn;
   };
   double s0 = 0, s1 = 0;
   int64_t g = g0 + threadIdx.x;
@@ -2446,13 +2446,23 @@ __global__ __launch_bounds__(1024) void pois_step_rr_kernel(double* __restrict__
   }
 }
 
-// p = r + beta p with beta = rr_new / rr
-__global__ void pois_dir_kernel(double* __restrict__ pv, const double* __restrict__ r,
-                                const double* __restrict__ rr_new, const double* __restrict__ rr, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double be = rr[0] > 0.0 ? rr_new[0] / rr[0] : 0.0;
-  pv[i] = r[i] + be * pv[i];
+// p = r + beta p with beta = rr_new / rr; every workgroup adds the nch <= kPoisChunks partials of rr_new
+// itself, in one fixed order, and the first stores it: no launch between the two for a single sum
+__global__ __launch_bounds__(256) void pois_dir_kernel(double* __restrict__ pv, const double* __restrict__ r,
+                                                       const double* __restrict__ part, int nch,
+                                                       double* __restrict__ rr_new, const double* __restrict__ rr,
+                                                       int64_t n) {
+  __shared__ double red[4];
+  const int t = threadIdx.x;
+  double s = t < nch ? part[t] : 0.0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((t & 63) == 0) red[t >> 6] = s;
+  __syncthreads();
+  s = (red[0] + red[1]) + (red[2] + red[3]);
+  if (blockIdx.x == 0 && t == 0) *rr_new = s;
+  const double be = rr[0] > 0.0 ? s / rr[0] : 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256) pv[i] = r[i] + be * pv[i];
 }
 
 // phi = P y with the FE part's GLL-mass-weighted mean removed: phi_g = m_g^-1/2 y_g - (z . y) / (z . z)
@@ -2465,7 +2475,7 @@ __global__ void pois_finish_fe_kernel(const double* __restrict__ y, const double
 
 struct PoisLayout {
   StepWork step;
-  double *x, *r, *p, *q, *v, *z, *f, *cO, *dscr, *sc, *part;
+  double *x, *r, *p, *q, *v, *z, *f, *cO, *dscr, *sc, *part, *pq_part;
   size_t total;
 };
 
@@ -2492,6 +2502,7 @@ PoisLayout pois_layout(const oefe_op_s* op, void* work) {
   L.dscr = take(256 * sizeof(double));
   L.sc = take(16 * sizeof(double));
   L.part = take(2 * kPoisPartials * sizeof(double));
+  L.pq_part = take((size_t)pq_partials(op) * sizeof(double));
   L.total = (size_t)(p - (char*)work);
   return L;
 }
@@ -2609,17 +2620,22 @@ static int poisson_solve_impl(oefe_op pop, const double* rho, const double* rho_
   int it = 0;
   double rel = 1.0;
   bool done = false;
-  const int nch1 = dot1_chunk_count(n);  // the r . r partials of pois_step_rr_kernel fill nch1 <= 128 of dscr
+  const int nch1 = (int)std::max<int64_t>(1, std::min<int64_t>(kPoisChunks, (n + 1023) / 1024));  // fill nch1 of dscr
+  const unsigned ndir = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
+  StepWork sw = L.step;
+  const bool pq = pq_in_step(op);
+  if (pq) {
+    sw.pq = L.sc + 2;
+    sw.pq_part = L.pq_part;
+  }
   while (!done && it < max_iter) {
     const int k = it & 1;
-    rc = apply_step<double>(op, false, L.p, 1, nullptr, L.q, 1, 1, 1.0, 0.0, 0.0, L.step, s);
-    if (!rc) rc = dot_columns<double>(false, L.p, 1, L.q, 1, n, 1, nullptr, L.sc + 2, L.dscr, s);
+    rc = apply_step<double>(op, false, L.p, 1, nullptr, L.q, 1, 1, 1.0, 0.0, 0.0, sw, s);
+    if (!rc && !pq) rc = dot_columns<double>(false, L.p, 1, L.q, 1, n, 1, nullptr, L.sc + 2, L.dscr, s);
     if (rc) return fail(rc, "oefe_poisson_solve: kernel launch failed");
     hipLaunchKernelGGL(pois_step_rr_kernel, dim3((unsigned)nch1), dim3(1024), 0, s, L.x, L.r, L.p, L.q, L.sc + k,
                        L.sc + 2, n, (n + nch1 - 1) / nch1, L.dscr);
-    rc = dot1_final(L.dscr, nch1, L.sc + (k ^ 1), s);
-    if (rc) return fail(rc, "oefe_poisson_solve: kernel launch failed");
-    hipLaunchKernelGGL(pois_dir_kernel, blocks(n), dim3(256), 0, s, L.p, L.r, L.sc + (k ^ 1), L.sc + k, n);
+    hipLaunchKernelGGL(pois_dir_kernel, dim3(ndir), dim3(256), 0, s, L.p, L.r, L.dscr, nch1, L.sc + (k ^ 1), L.sc + k, n);
     ++it;
     if (it % 8 == 0 || it == max_iter) {  // convergence test: one host read every 8 iterations
       hipError_t e = hipMemcpyAsync(hbuf, L.sc, 4 * sizeof(double), hipMemcpyDeviceToHost, s);

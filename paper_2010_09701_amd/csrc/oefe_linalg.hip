@@ -2547,13 +2547,6 @@ int dot_columns(bool cplx, const T* A, int64_t lda, const T* B, int64_t ldb, int
   return check();
 }
 size_t dot_scratch_bytes(int nv) { return ((size_t)kDotChunks * cdiv(nv, 256)) * sizeof(double); }
-int dot1_chunk_count(int64_t n) { return gram_chunks(n); }
-
-int dot1_final(const double* part, int nch, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(dot_final_kernel, dim3(1), dim3(256), 0, s, part, nch, nullptr, out);
-  return check();
-}
-
 template int dot_columns<double>(bool, const double*, int64_t, const double*, int64_t, int64_t, int, const double*,
                                  double*, double*, hipStream_t);
 template int dot_columns<float>(bool, const float*, int64_t, const float*, int64_t, int64_t, int, const double*,

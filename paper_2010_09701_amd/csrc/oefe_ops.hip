@@ -60,6 +60,8 @@ struct KP {
   T* part2;
   int nch;  // chunks per function in part2
   T* wp;
+  double* pq;  // one real column: receives x . out (null: not wanted), and its partials per node workgroup
+  double* pq_part;
   const T* wv;  // W (V + the form's constant shift) of this operator at its quadrature points
   const T* tv;
   const T* S;
@@ -1814,8 +1816,10 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
                                                            const int32_t* __restrict__ tile_fns, int ntiles, int tm,
                                                            int pad) {
   const KP<T>& P = kb.k[blockIdx.z];
-  const int t = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform per wave
-  if (t >= ntiles) return;  // the whole wave
+  const int tw = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));  // uniform per wave
+  __shared__ double red[4];
+  const bool live = tw < ntiles;  // a wave past the last tile repeats it and stores nothing
+  const int t = live ? tw : ntiles - 1;
   const int r = (int)threadIdx.x & 63;
   int x0, y0, z0, ix, iy, iz;
   tile_origin(t, n, tm, x0, y0, z0);
@@ -1853,11 +1857,11 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
     // four functions at a time: their loads issued together, their butterflies interleaved
     for (int fb = 0; fb < FP; fb += 4) {
       T h[4], z[4], q[4];
+      __builtin_memcpy(h, __builtin_assume_aligned(tv + fb, 2 * sizeof(T)), sizeof(h));  // (FP, pad and offsets are even)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         // padding entries of the list hold -1 (and zero coupling values): Z^O row 0, replaced by 0
         const int fn = tile_fns[f0 + fb + i];
-        h[i] = tv[fb + i];
         const T zl = P.zo[(int64_t)max(fn, 0) * P.ncr];
         z[i] = fn >= 0 ? zl : T(0);
       }
@@ -1866,20 +1870,28 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
         acc = fma(h[i], z[i], acc);
         q[i] = h[i] * xv;
       }
+      // the four sums over the 64 rows: halves of the wave take two functions each, quarters one, so
+      // a batch needs 7 exchanges, not 24 (the LDS permutes bound this kernel: diamond64 30.9 -> 24.9 us)
+      const bool h32 = r & 32, h16 = r & 16;
+      T s0 = (h32 ? q[2] : q[0]) + __shfl_xor(h32 ? q[0] : q[2], 32);
+      T s1 = (h32 ? q[3] : q[1]) + __shfl_xor(h32 ? q[1] : q[3], 32);
+      T sq = (h16 ? s1 : s0) + __shfl_xor(h16 ? s0 : s1, 16);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) q[i] += __shfl_xor(q[i], o);
-      if (r == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) P.part[(int64_t)(f0 + fb + i) * P.ncr] = q[i];
-      }
+      for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+      if ((r & 15) == 0 && live) P.part[(int64_t)(f0 + fb + (h32 ? 2 : 0) + (h16 ? 1 : 0)) * P.ncr] = sq;
     }
   }
-  if (ok) {
-    T o = alpha * acc;
-    if (beta != T(0)) o -= beta * pv;
-    P.out[(int64_t)g * P.ldo] = o;
+  T o = alpha * acc;
+  if (beta != T(0)) o -= beta * pv;
+  if (ok && live) P.out[(int64_t)g * P.ldo] = o;
+  if (P.pq) {
+    // x . out of the workgroup's rows (the conjugate gradients' p . q without a pass of its own)
+    double v = ok && live ? (double)xv * (double)o : 0.0;
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) v += __shfl_xor(v, k);
+    if (r == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) P.pq_part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
   }
 }
 
@@ -2008,6 +2020,69 @@ template <typename T, bool CPLX>
 __global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, ChainArgs ca) {
   extern __shared__ __align__(16) unsigned char chain_raw[];
   enr_chain<T, CPLX, kChainCols>(kb, ca, (int)blockIdx.x, chain_raw);
+}
+
+// The chain of one real column outside a recurrence: 16 lanes of a row share its sums (the chunk partials,
+// or with fn_pptr the tile partials themselves, and the products), their parts added by a fixed butterfly,
+// S and H^oo from memory.  enr_chain_kernel, laid out for 16 columns, computes each sum 16 times over and
+// stages both matrices first: 12.3 us for 64 functions, 7.0 so.  With npq also x . out, from the node
+// workgroups' partials and the enrichment rows.
+constexpr int kCol1ChainMax = 4096;
+template <typename T>
+__global__ __launch_bounds__(1024) void enr_col1_kernel(KBatch<T> kb, int64_t N, int n,
+                                                        const int32_t* __restrict__ fn_pptr,
+                                                        const int32_t* __restrict__ fn_poff, int npq) {
+  extern __shared__ __align__(16) unsigned char col1_raw[];
+  T* Ws = reinterpret_cast<T*>(col1_raw);  // [n] W'
+  __shared__ double red[16];
+  const KP<T>& P = kb.k[blockIdx.z];
+  const int t = (int)threadIdx.x, jl = t & 15;
+  auto sum16 = [](T v) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
+    return v;
+  };
+  T alpha, cst, beta;
+  step_scalars(P, alpha, cst, beta);
+  double v = 0.0;
+  for (int k = t; k < npq; k += 1024) v += P.pq_part[k];
+  for (int i = t >> 4; i < n; i += 64) {
+    T w = 0, h = 0;
+    if (fn_pptr) {
+      for (int e = fn_pptr[i] + jl; e < fn_pptr[i + 1]; e += 16) w += P.part[(int64_t)fn_poff[e] * P.ncr];
+    } else {
+#pragma unroll 4
+      for (int ch = jl; ch < P.nch; ch += 16) w += P.part2[((int64_t)i * P.nch + ch) * P.ncr];
+    }
+#pragma unroll 4
+    for (int k = jl; k < n; k += 16) h += P.Hoo[(int64_t)i * n + k] * P.zo[(int64_t)k * P.ncr];
+    w = sum16(w + h);
+    if (jl == 0) Ws[i] = w;
+  }
+  __syncthreads();
+  for (int i = t >> 4; i < n; i += 64) {
+    const T xv = P.x[(N + i) * P.ldx], pv = beta != T(0) ? P.prev[(N + i) * P.ldo] : T(0);
+    T a = 0;
+#pragma unroll 4
+    for (int k = jl; k < n; k += 16) a += P.S[(int64_t)i * n + k] * Ws[k];
+    a = sum16(a);
+    T o = alpha * (a - cst * xv);
+    if (beta != T(0)) o -= beta * pv;
+    if (jl == 0) {
+      P.out[(N + i) * P.ldo] = o;
+      v += (double)xv * (double)o;
+    }
+  }
+  if (!npq) return;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((t & 63) == 0) red[t >> 6] = v;
+  __syncthreads();
+  if (t == 0) {
+    double sum = 0.0;
+    for (int w = 0; w < 16; ++w) sum += red[w];
+    *P.pq = sum;
+  }
 }
 
 // diagonal test operator: out = alpha (lambda x - c x) - beta prev
@@ -2471,6 +2546,18 @@ void launch_cell_bf16(const oefe_op_s* op, const KBatch<float>& kb, hipStream_t 
                      lds, s, kb, op->d.bf_mats, op->cf, op->nc, op->p, op->n, op->P1, op->n_cells);
 }
 
+}  // namespace
+
+// Whether a step of one real column outside a recurrence can form x . out as it goes: the flat node
+// kernel and the chain in one launch.
+bool pq_in_step(const oefe_op_s* op) {
+  return !op->cplx && !op->diagonal && op->n_enr > 0 && op->tile_fpmax <= kCol1MaxFunctions &&
+         op->n_enr <= kCol1ChainMax;
+}
+int64_t pq_partials(const oefe_op_s* op) { return cdiv(tile_count(op->n, op->tile_mode), 4); }
+
+namespace {
+
 template <typename T, bool CPLX>
 int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipStream_t s, const Overlap* ov,
                           bool bf16) {
@@ -2515,7 +2602,10 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
       nO > 0 && clds <= 96 * 1024 &&
       allow_dynamic_lds(reinterpret_cast<const void*>(&enr_chain_kernel<T, CPLX>), clds) == hipSuccess;
   // few partials per function (small meshes): the chain folds them itself, one launch fewer
-  const bool direct = one_chain && op->fn_smax <= kReduceChunk;
+  const bool direct = (one_chain || (!CPLX && !ovl && max_nv == 1 && nO <= kCol1ChainMax)) && op->fn_smax <= kReduceChunk;
+  const bool pq = kb.k[0].pq != nullptr;
+  const bool col1_chain = !CPLX && !ovl && max_nv == 1 && nO > 0 && nO <= kCol1ChainMax;
+  if (pq && !(col1_chain && pq_in_step(op))) return OEFE_EINVAL;
   // fold of the tile partials, and the chain that forms W' from it and writes the enrichment rows of
   // out (and, in an overlapped recurrence, Z^O of the next step), on stream se
   auto fold = [&](hipStream_t se) {
@@ -2525,7 +2615,11 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
                        dim3(256), 0, se, kb, nch, op->d.fn_pptr, op->d.fn_poff);
   };
   auto chain = [&](hipStream_t se) {
-    if (one_chain) {
+    if (col1_chain) {
+      if constexpr (!CPLX)
+        hipLaunchKernelGGL((enr_col1_kernel<T>), dim3(1, 1, nk), dim3(1024), (size_t)nO * sizeof(T), se, kb, op->N, nO,
+                           direct ? op->d.fn_pptr : nullptr, op->d.fn_poff, pq ? (int)pq_partials(op) : 0);
+    } else if (one_chain) {
       const ChainArgs c{op->N, nO, (ovl && !ov->last) ? 1 : 0, direct ? op->d.fn_pptr : nullptr, op->d.fn_poff, 0, false};
       hipLaunchKernelGGL((enr_chain_kernel<T, CPLX>), dim3((unsigned)cdiv(max_nv, kChainCols), 1, nk), dim3(1024), clds,
                          se, kb, c);
@@ -2632,6 +2726,8 @@ KP<T> make_kp(const oefe_op_s* op, const T* x, int64_t ld, const T* prev, T* out
   P.part2 = (T*)w.part2;
   P.nch = reduce_chunks(op);
   P.wp = (T*)w.wp;
+  P.pq = w.pq;
+  P.pq_part = w.pq_part;
   P.wv = dp.WV;
   P.tv = dp.tv;
   P.S = dp.S;
