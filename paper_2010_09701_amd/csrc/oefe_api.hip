@@ -141,8 +141,8 @@ Layout layout(const oefe_op_s* op, int prec, int nv, void* work) {
   L.Rinv = (double*)p; p += sq + al256(nv * sizeof(double));
   L.U = (double*)p; p += sq;
   L.lam = (double*)p; p += al256(nv * sizeof(double));
-  const size_t gs = al256(std::max(gram_scratch_bytes(cplx, nv, nv, op->n_tot),
-                                   dot_scratch_bytes(nv)));
+  const size_t gs = al256(std::max({gram_scratch_bytes(cplx, nv, nv, op->n_tot),
+                                    gram_scratch_bytes(cplx, nv, 1, op->n_tot), dot_scratch_bytes(nv)}));
   L.gscr = (double*)p; p += gs;
   L.jscr = (double*)p; p += al256(jacobi_scratch_bytes(cplx, nv));
   L.misc = (double*)p; p += 512 * sizeof(double);
@@ -2074,7 +2074,6 @@ int lanczos_bounds(oefe_op op, int32_t k, const double* v0, double* out, void* w
   const int64_t n = op->n_tot;
   double* Vb = (double*)L.vecA;  // [n x kb]
   double* w = (double*)L.vecB;   // [n x 1] (uses the first n*E doubles)
-  double* t = w + n * E;         // [n x 1]
   StepWork sw = carve_step_work(op, 8, cplx, 1, work);
   double* a_d = L.misc;       // alpha_j at misc[2 j] (complex slot), beta_j at misc[256 + j], norm at misc[511]
   double* h = L.G;            // reorth coefficients [kb]
@@ -2098,8 +2097,7 @@ int lanczos_bounds(oefe_op op, int32_t k, const double* v0, double* out, void* w
     // full reorthogonalization, twice: w -= V (V^* w)
     for (int r = 0; r < 2 && !rc; ++r) {
       rc = gram(cplx, Vb, kb, j + 1, w, 1, 1, n, h, 1, L.gscr, (size_t)1 << 62, s);
-      if (!rc) rc = gemm_nn(cplx, Vb, kb, h, 1, t, 1, n, j + 1, 1, s);
-      if (!rc) rc = sub_block(cplx, w, t, n, s);
+      if (!rc) rc = sub_gemv(cplx, w, Vb, kb, h, j + 1, n, s);
     }
     // beta_j = ||w||
     if (!rc) rc = dot_columns<double>(cplx, w, 1, w, 1, n, 1, nullptr, a_d + 256 + j, L.gscr, s);

@@ -126,7 +126,8 @@ int lanczos_axpy(bool cplx, double* w, const double* v, const double* vprev, con
                  const double* beta, int64_t n, int64_t ldv, hipStream_t s);
 int lanczos_scale(bool cplx, double* dst, int64_t ldd, const double* w, const double* beta, int64_t n,
                   hipStream_t s);
-int sub_block(bool cplx, double* w, const double* t, int64_t n, hipStream_t s);
+// w -= V h, V [n x k] (ld)
+int sub_gemv(bool cplx, double* w, const double* V, int64_t ld, const double* h, int k, int64_t n, hipStream_t s);
 int sqrt_inplace(double* x, hipStream_t s);
 
 }  // namespace oefe

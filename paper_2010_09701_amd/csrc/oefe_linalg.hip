@@ -69,6 +69,54 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const double* __restr
   }
 }
 
+// G = A^* b for a single column b (the Lanczos coefficients), partial[chunk][i] over a chunk of rows: thread
+// t takes column i = t mod na of the rows t / na, t / na + 256 / na, ..., four in flight, so that
+// neighbouring threads read neighbouring entries of a row; a column's threads are added in order.  The
+// 16 x 16 tiles of gram_partial_kernel leave 15 of 16 columns of B idle: 11 columns of 514 / 110 k / 885 k
+// rows 11 / 40 / 317 us there, XX here.
+template <bool CPLX>
+__global__ __launch_bounds__(256) void gram_vec_kernel(const double* __restrict__ A, int64_t lda, int na,
+                                                       const double* __restrict__ b, int64_t ldb, int64_t n,
+                                                       int64_t rows_per_chunk, double* __restrict__ part) {
+  constexpr int E = CPLX ? 2 : 1;
+  __shared__ double red[256 * E];
+  const int t = threadIdx.x, rstep = 256 / na, row = t / na, i = t - row * na;
+  const int64_t g0 = (int64_t)blockIdx.x * rows_per_chunk, g1 = min(n, g0 + rows_per_chunk);
+  double sr = 0.0, si = 0.0;
+  if (row < rstep) {
+    double pr[4] = {0, 0, 0, 0}, pi[4] = {0, 0, 0, 0};
+    auto term = [&](int64_t g, double& vr, double& vi) {
+      const double* x = A + (g * lda + i) * E;
+      const double* y = b + g * ldb * E;
+      if constexpr (!CPLX) {
+        vr += x[0] * y[0];
+      } else {
+        vr += x[0] * y[0] + x[1] * y[1];
+        vi += x[0] * y[1] - x[1] * y[0];
+      }
+    };
+    int64_t g = g0 + row;
+    for (; g + 3 * rstep < g1; g += 4 * rstep)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) term(g + u * rstep, pr[u], pi[u]);
+    for (; g < g1; g += rstep) term(g, pr[0], pi[0]);
+    sr = (pr[0] + pr[1]) + (pr[2] + pr[3]);
+    si = (pi[0] + pi[1]) + (pi[2] + pi[3]);
+  }
+  red[t * E] = sr;
+  if (CPLX) red[t * E + E - 1] = si;
+  __syncthreads();
+  if (t < na) {
+    for (int q = 1; q < rstep; ++q) {
+      sr += red[(q * na + t) * E];
+      if (CPLX) si += red[(q * na + t) * E + E - 1];
+    }
+    double* o = part + ((int64_t)blockIdx.x * na + t) * E;
+    o[0] = sr;
+    if (CPLX) o[E - 1] = si;
+  }
+}
+
 template <bool CPLX>
 __global__ void gram_reduce_kernel(const double* __restrict__ part, int nchunks, int na, int nb,
                                    double* __restrict__ G, int ldg) {
@@ -1741,9 +1789,27 @@ __global__ void lanczos_scale_kernel(double* __restrict__ dst, int64_t ldd, cons
   dst[r * ldd * E + e] = w[(dst == w ? r * ldd * E : r * E) + e] / beta[0];
 }
 
-__global__ void sub_kernel(double* __restrict__ w, const double* __restrict__ t, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) w[i] -= t[i];
+// w -= V h (k columns of a basis, one thread per row, in column order): the reorthogonalization's second
+// half in one pass over V, where a product into a vector and a subtraction took two launches
+template <bool CPLX>
+__global__ __launch_bounds__(256) void sub_gemv_kernel(double* __restrict__ w, const double* __restrict__ V, int64_t ld,
+                                                       const double* __restrict__ h, int k, int64_t n) {
+  constexpr int E = CPLX ? 2 : 1;
+  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= n) return;
+  const double* v = V + g * ld * E;
+  double sr = 0.0, si = 0.0;
+#pragma unroll 4
+  for (int j = 0; j < k; ++j) {
+    if constexpr (!CPLX) {
+      sr += v[j] * h[j];
+    } else {
+      sr += v[2 * j] * h[2 * j] - v[2 * j + 1] * h[2 * j + 1];
+      si += v[2 * j] * h[2 * j + 1] + v[2 * j + 1] * h[2 * j];
+    }
+  }
+  w[g * E] -= sr;
+  if (CPLX) w[g * E + E - 1] -= si;
 }
 
 __global__ void sqrt_kernel(double* x) { x[0] = sqrt(x[0]); }
@@ -1808,6 +1874,9 @@ static bool gram_pairs(const double* A, int64_t lda, int na, const double* B, in
 // entries of a real 2 na x 2 nb Gram matrix (as many multiplications as the complex one; with A = B half
 // of them by symmetry).  110 k rows, 96 columns: 290 + 36 -> 187 + 12 us (partials, reduction).
 static bool gram_as_real(bool cplx, int na, int nb) { return cplx && na >= 8 && nb >= 8; }
+// one column on the right: chunks of at least 64 rows, up to 512
+static bool gram_vec(int na, int nb) { return nb == 1 && na <= 128; }
+static int gram_vec_chunks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(512, cdiv(n, 64))); }
 static size_t gram_real_bytes(int na, int nb) { return ((size_t)4 * na * nb * sizeof(double) + 255) / 256 * 256; }
 
 __global__ __launch_bounds__(256) void gram_combine_kernel(const double* __restrict__ R, int na, int nb,
@@ -1822,6 +1891,7 @@ __global__ __launch_bounds__(256) void gram_combine_kernel(const double* __restr
 }
 
 size_t gram_scratch_bytes(bool cplx, int na, int nb, int64_t n) {
+  if (gram_vec(na, nb)) return (size_t)gram_vec_chunks(n) * na * (cplx ? 2 : 1) * sizeof(double);
   if (gram_as_real(cplx, na, nb)) return gram_real_bytes(na, nb) + gram_scratch_bytes(false, 2 * na, 2 * nb, n);
   if (gram_mfma_tiled(cplx, na, nb)) {
     const int gi = (int)cdiv(na, 16 * kGramNBMax), gj = (int)cdiv(nb, 16 * kGramNBMax);
@@ -1860,6 +1930,19 @@ static void launch_gram_mfma(const double* A, int64_t lda, int na, const double*
 int gram(bool cplx, const double* A, int64_t lda, int na, const double* B, int64_t ldb, int nb, int64_t n, double* G,
          int ldg, double* scratch, size_t scratch_bytes, hipStream_t s) {
   if (gram_scratch_bytes(cplx, na, nb, n) > scratch_bytes) return OEFE_EINVAL;
+  if (gram_vec(na, nb)) {
+    const int nch = gram_vec_chunks(n);
+    const int64_t rpc = cdiv(n, nch);
+    const dim3 g2((unsigned)cdiv(na, 4));
+    if (cplx) {
+      hipLaunchKernelGGL(gram_vec_kernel<true>, dim3(nch), dim3(256), 0, s, A, lda, na, B, ldb, n, rpc, scratch);
+      hipLaunchKernelGGL(gram_reduce_wave_kernel<true>, g2, dim3(256), 0, s, scratch, nch, na, 1, G, ldg);
+    } else {
+      hipLaunchKernelGGL(gram_vec_kernel<false>, dim3(nch), dim3(256), 0, s, A, lda, na, B, ldb, n, rpc, scratch);
+      hipLaunchKernelGGL(gram_reduce_wave_kernel<false>, g2, dim3(256), 0, s, scratch, nch, na, 1, G, ldg);
+    }
+    return check();
+  }
   if (gram_as_real(cplx, na, nb)) {
     const size_t rb = gram_real_bytes(na, nb);
     const int rc = gram(false, A, 2 * lda, 2 * na, B, 2 * ldb, 2 * nb, n, scratch, 2 * nb, scratch + rb / sizeof(double),
@@ -2594,9 +2677,12 @@ int lanczos_scale(bool cplx, double* dst, int64_t ldd, const double* w, const do
   return check();
 }
 
-int sub_block(bool cplx, double* w, const double* t, int64_t n, hipStream_t s) {
-  const int64_t m = n * (cplx ? 2 : 1);
-  hipLaunchKernelGGL(sub_kernel, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, s, w, t, m);
+int sub_gemv(bool cplx, double* w, const double* V, int64_t ld, const double* h, int k, int64_t n, hipStream_t s) {
+  const dim3 grid((unsigned)cdiv(n, 256));
+  if (cplx)
+    hipLaunchKernelGGL(sub_gemv_kernel<true>, grid, dim3(256), 0, s, w, V, ld, h, k, n);
+  else
+    hipLaunchKernelGGL(sub_gemv_kernel<false>, grid, dim3(256), 0, s, w, V, ld, h, k, n);
   return check();
 }
 
