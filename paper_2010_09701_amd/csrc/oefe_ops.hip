@@ -2521,13 +2521,15 @@ int launch_node_nc(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRu
 }
 
 // float32: two columns per lane, so that a wave's row segments fill 128-byte lines; a single real
-// column takes one per lane
+// column takes one per lane, and so do real blocks that groups of 32 columns would pad by more than 15 %
+// over groups of 16 (diamond8, 72 columns: 62 -> 59 us and a degree 96.5 -> 93.5; a column's sums are the same)
 template <typename T, bool CPLX>
 int launch_node(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRun run, hipStream_t s) {
   if constexpr (sizeof(T) == 4) {
     int min_ncr = max_ncr;
     for (int q = 0; q < kb.nk; ++q) min_ncr = std::min(min_ncr, kb.k[q].ncr);
-    if (CPLX || min_ncr >= 2) return launch_node_nc<T, CPLX, 2>(op, kb, max_ncr, run, s);
+    const bool narrow = !CPLX && 20 * cdiv(max_ncr, 32) * 32 > 23 * cdiv(max_ncr, 16) * 16;
+    if (CPLX || (min_ncr >= 2 && !narrow)) return launch_node_nc<T, CPLX, 2>(op, kb, max_ncr, run, s);
   }
   if constexpr (sizeof(T) == 8 || !CPLX) return launch_node_nc<T, CPLX, 1>(op, kb, max_ncr, run, s);
   return OEFE_EINVAL;
