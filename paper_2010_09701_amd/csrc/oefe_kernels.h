@@ -37,6 +37,8 @@ StepWork carve_step_work(const oefe_op_s* op, int elem_bytes, bool cplx, int nv,
 // `side` beside step k's cell and node stages; then, after the node stage (ev_node), which formed step
 // k+1's partials from its result, their fold beside the cell stage of step k+1, whose node stage waits
 // for it (ev_zo).
+// Small blocks take the chain in the cell launch and the fold on the main stream instead (the events and
+// `side` unused).
 // first: this step computes its own Z^O and partials; last: the main stream waits for the side
 // chain at the end of the step.
 struct Overlap {
