@@ -1417,12 +1417,19 @@ __device__ __forceinline__ bool node_item(const KP<T>& P, const NodeMesh& g, con
 
 // Barrier of the workgroup for LDS written by its waves; loads from memory stay under way
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// Barrier for the blocks and lists copied by node_item: a wave's copies were issued before the load of v
-// and loads complete in order, so they are in LDS once v is here
+// Barrier for the blocks and lists copied by node_item, without waiting for the loads issued after v: a
+// wave's copies were issued before the load of v and loads complete in order, so they are in LDS once v is
+// here.  v has to be the loaded value itself, of a load that every wave issues: behind a select the compiler
+// may turn the load into a branch around it, and a wave without an active lane there would wait for nothing.
 template <typename V>
 __device__ __forceinline__ void copied_barrier(V v) {
   asm volatile("" ::"v"(v));
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The same, waiting for everything the wave has under way
+__device__ __forceinline__ void copied_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // part_t[f][columns] = Ht_t^* X_t, in two parts: the two waves of a column group put their rows of X_t
@@ -1529,7 +1536,7 @@ __global__ __launch_bounds__(128 * kNodeGroups, 4) void fe_part_kernel(KBatch<T>
 #pragma unroll
       for (int j = 0; j < NC; ++j) x[rb][v].e[j] = gr >= 0 ? x[rb][v].e[j] : T(0);
     }
-  copied_barrier(x[1][3].e[0]);
+  copied_barrier();  // (x went through selects: no value of it stands for the copies)
   T* xt = reinterpret_cast<T*>(smem_raw + lds.x);
   node_stash<T, NC>(xt, it, x);
   node_part<T, CPLX, NC>(P, reinterpret_cast<const T*>(smem_raw + it.blk), it.FP + g.pad, xt, it);
