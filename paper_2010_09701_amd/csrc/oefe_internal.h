@@ -80,6 +80,11 @@ __host__ __device__ inline int tile_node(int t, int r, int n, int mode) {
   tile_origin(t, n, mode, x0, y0, z0);
   return tile_row_node(x0, y0, z0, r, n, mode);
 }
+// Position (bx, by, bz) of the node-slot grid, S = nc (p + 1) slots per edge: up to S^3 of them, past 2^31
+// from S = 1291
+__host__ __device__ inline int64_t slot_index(int bx, int by, int bz, int S) {
+  return bx + S * (by + (int64_t)S * bz);
+}
 // Storage of a tile's dense coupling block: rows of FP + pad elements (FP: the tile's padded function
 // count, a multiple of 4).  pad = 2: the block can be copied to LDS as it is and 32 lanes reading two
 // functions of 16 rows touch distinct banks (float64: twice the stride is 4 mod 8), with rows aligned

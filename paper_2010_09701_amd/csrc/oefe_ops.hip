@@ -1403,7 +1403,7 @@ __device__ __forceinline__ bool node_item(const KP<T>& P, const NodeMesh& g, con
                 bz = qz * g.P1 + (rz ? rz + 1 : 0);
       NodeRow<T> r;
       r.row = in ? ix + g.n * (iy + g.n * iz) : 0;
-      r.slot = in ? (int64_t)(bx + S * (by + S * bz)) * P.ldc : 0;
+      r.slot = in ? slot_index(bx, by, bz, S) * P.ldc : 0;
       r.msc = cf->mscale * cf->om[rx] * cf->om[ry] * cf->om[rz];
       r.dx = in && rx == 0 ? P.ldc : 0;
       r.flags = in ? kIn | (ry == 0 ? kY2 : 0) | (rz == 0 ? kZ2 : 0) | (bx == 0 ? kXW : 0) | (by == 0 ? kYW : 0) |
@@ -1845,7 +1845,7 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
   const T msc = cf.mscale * cf.om[rx] * cf.om[ry] * cf.om[rz];
   const int S = nc * P1;
   const int64_t ldc = P.ldc, Sl = (int64_t)S * ldc, S2l = Sl * S;
-  const T* __restrict__ Y0 = P.ycell + (bx + (int64_t)S * (by + (int64_t)S * bz)) * ldc;
+  const T* __restrict__ Y0 = P.ycell + slot_index(bx, by, bz, S) * ldc;
   const T m2 = x2 ? T(1) : T(0);
   T sum = 0;
 #pragma unroll
