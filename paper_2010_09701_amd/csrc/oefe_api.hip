@@ -1668,6 +1668,14 @@ int oefe_set_launch_shape(oefe_op op, int32_t cw, int32_t cb) {
 }  // extern "C"
 
 namespace {
+// Whether one launch can serve both operators: it takes the mesh, the coefficients, the tile lists and the
+// storage of the coupling blocks (poisson: its cell scale and row stride) from the first
+bool same_layout(const oefe_op_s* a, const oefe_op_s* b) {
+  return b->nc == a->nc && b->p == a->p && b->L == a->L && b->n_enr == a->n_enr && b->n_tiles == a->n_tiles &&
+         b->tile_mode == a->tile_mode && b->tile_slots == a->tile_slots && b->tile_fpmax == a->tile_fpmax &&
+         b->poisson == a->poisson && b->tile_pad == a->tile_pad;
+}
+
 // Launch-shape tuner: times one batched operator step (out = alpha (Ht x - c x) - beta out,
 // the filter's access pattern and stream overlap, bounded values) for each candidate
 // cell-tile width cw and node-stage column width cb, and keeps the fastest on every operator.
@@ -1842,11 +1850,7 @@ int chebyshev_filter_batched(int32_t nk, const oefe_op* ops, oefe_prec prec, voi
   for (int q = 0; q < nk; ++q) {
     if (!ops[q] || !X[q] || nv[q] <= 0 || ld[q] < nv[q]) return fail(OEFE_EINVAL, "bad per-operator arguments");
     if (int rc = check_prec(ops[q], prec)) return rc;
-    const oefe_op_s* a = ops[0];
-    const oefe_op_s* b = ops[q];
-    if (b->diagonal || a->diagonal || b->nc != a->nc || b->p != a->p || b->L != a->L || b->n_enr != a->n_enr ||
-        b->n_tiles != a->n_tiles || b->tile_mode != a->tile_mode || b->tile_slots != a->tile_slots ||
-        b->tile_fpmax != a->tile_fpmax)
+    if (ops[0]->diagonal || ops[q]->diagonal || !same_layout(ops[0], ops[q]))
       return fail(OEFE_EINVAL, "batched operators must share the mesh and the enrichment layout");
     const double aa = abc[3 * q], bb = abc[3 * q + 1], a0 = abc[3 * q + 2];
     if (!(aa < bb) || !(a0 < aa)) return fail(OEFE_EINVAL, "need a0 < a < b for every operator");
@@ -1869,11 +1873,7 @@ int oefe_autotune(int32_t nk, const oefe_op* ops, oefe_prec prec, void* const* X
   for (int q = 0; q < nk; ++q) {
     if (!ops[q] || ops[q]->diagonal || !X[q] || nv[q] <= 0 || ld[q] < nv[q]) return fail(OEFE_EINVAL, "bad block");
     if (int rc = check_prec(ops[q], prec)) return rc;
-    const oefe_op_s* a = ops[0];
-    const oefe_op_s* b = ops[q];
-    if (b->nc != a->nc || b->p != a->p || b->L != a->L || b->n_enr != a->n_enr || b->cplx != a->cplx ||
-        b->n_tiles != a->n_tiles || b->tile_mode != a->tile_mode || b->tile_slots != a->tile_slots ||
-        b->tile_fpmax != a->tile_fpmax)
+    if (ops[q]->cplx != ops[0]->cplx || !same_layout(ops[0], ops[q]))
       return fail(OEFE_EINVAL, "operators must share mesh and enrichment layout");
   }
   hipStream_t s = (hipStream_t)stream;
