@@ -2692,7 +2692,10 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
     const int kind = CPLX && nO > 0 && op->timer_kind == OEFE_TIMER_COUPLING ? OEFE_TIMER_COUPLING : OEFE_TIMER_NODE;
     const NodeRun run = !ahead ? NodeRun::node_px : ov->last ? NodeRun::node : NodeRun::node_pnext;
     timed(kind, s, [&] { rc = launch_node<T, CPLX>(op, kb, max_ncr, run, s); });
-    if (rc) return rc;
+    if (rc) {  // the chain is queued: the caller's stream waits for ev_zo
+      if (nO > 0 && ahead && !inl) (void)hipEventRecord(ov->ev_zo, ov->side);
+      return rc;
+    }
   }
   if (inl) {
     if (!ov->last) fold(s);

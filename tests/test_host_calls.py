@@ -30,3 +30,25 @@ def test_batch_of_unlike_operators_is_refused(rec):
         assert rec.batched(pair, F64, n_tot, 4, 2) == EINVAL
         assert rec.autotune(pair, F64, n_tot, 4)[0] == EINVAL
         assert rec.events() == []
+
+
+@pytest.mark.parametrize("m", [1, 3])
+def test_failed_node_launch_leaves_no_side_work(rec, m):
+    """A step whose node kernel cannot be launched returns with its enrichment chain queued on the side
+    stream: the caller's stream has to wait for it, because the chain writes into the caller's buffers."""
+    base = wl.tiny_system(nc=3, p=2, n_atoms=8, seed=13, L=6.0, r0=1.0, r1=2.9)
+    enr = [wl.EnrichmentFn(a, i // 4, 2.0 / (1 + i % 4), (i % 4) - 1) for a in range(8) for i in range(8)]
+    s = dataclasses.replace(base, enr=enr).with_k(np.array([0.21, -0.37, 0.13]))
+    op = rec.operator(s)  # 64 complex functions: chain and fold on the side stream, more than 64 KB of LDS a tile
+    rec.events()
+    rec.fail_attribute("fe_node_kernel")
+    try:
+        assert rec.filter(op, C128, s.n_tot, 1, m, stream=7) != 0
+    finally:
+        rec.fail_attribute()
+    ev = rec.events()
+    side = [i for i, e in enumerate(ev) if type(e).__name__ == "Launch" and e.stream != 7]
+    assert side and not any(type(e).__name__ == "Launch" and "fe_node_kernel" in e.kernel for e in ev)
+    joined = [i for i, e in enumerate(ev) if type(e).__name__ == "Record" and e.stream == ev[side[-1]].stream and i > side[-1]]
+    assert joined and any(type(e).__name__ == "Wait" and e.stream == 7 and e.event == ev[joined[-1]].event
+                          for e in ev[joined[-1]:])
