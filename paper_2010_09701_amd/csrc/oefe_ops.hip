@@ -459,7 +459,9 @@ __device__ __forceinline__ void wave_sync() {
 constexpr int kChainCols = 16;
 
 constexpr int kChainColsCell = 4;
-constexpr int64_t kChainInCellElems = (int64_t)1 << 23;  // real elements of the step's blocks (chain_in_cell)
+// most real elements of the step's blocks (chain_in_cell): with at least three workgroups a CU by the
+// chain's LDS, and below
+constexpr int64_t kChainInCellElems = (int64_t)1 << 23, kChainInCellElemsLarge = (int64_t)3 << 18;
 
 template <typename T, bool CPLX>
 constexpr size_t enr_chain_lds_bytes(int n, int cols = kChainCols) {
@@ -675,7 +677,11 @@ constexpr size_t cell_lanes_lds_bytes() { return 4 * (P1 * P1 * P1 * lanes_cw<P1
 // Gauss values, the x-derivative taken on the x-y plane before the transpose), weighted, from
 // the complex partner lane (real <-> imaginary part) with the sign of -i, into the values that
 // the backward passes project.
-template <typename T, int P1, bool CPLX, bool UF = false>
+//
+// FIRST: what the launch's first ca.nblk blocks do instead.  An instance of its own each: the registers of the
+// enrichment chain would be those of every cell block (complex128 degree 2: 64 without it, 108 with it).
+enum class CellFirst { none, zo, chain };
+template <typename T, int P1, bool CPLX, bool UF, CellFirst FIRST>
 __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, CellCoef<T> cf, int nc, int p, int n,
                                                             int64_t n_cells, int nch, ChainArgs ca) {
   static_assert(!UF || CPLX, "the first-derivative term acts on complex columns");
@@ -688,19 +694,21 @@ __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, Cel
   // XCD (workgroups bk = x mod 8) takes a contiguous range of L, so that the chunks reading
   // the same node rows, and neighbouring cells, share one L2
   extern __shared__ __align__(16) unsigned char cell_raw[];
-  if ((int)blockIdx.x < ca.nblk) {  // the enrichment chain of this step, or its Z^O
-    if (ca.zo_only)
-      enr_zo<T, CPLX>(kb, ca, (int)blockIdx.x);
-    else
-      enr_chain<T, CPLX, kChainColsCell>(kb, ca, (int)blockIdx.x, cell_raw);
+  if (FIRST != CellFirst::none && (int)blockIdx.x < ca.nblk) {  // the enrichment chain of this step, or its Z^O
+    if constexpr (FIRST == CellFirst::zo) enr_zo<T, CPLX>(kb, ca, (int)blockIdx.x);
+    if constexpr (FIRST == CellFirst::chain) enr_chain<T, CPLX, kChainColsCell>(kb, ca, (int)blockIdx.x, cell_raw);
     return;
   }
-  const int nbk = (int)gridDim.x - ca.nblk, bk = (int)blockIdx.x - ca.nblk, nb8 = nbk & ~7;
+  const int nfirst = FIRST == CellFirst::none ? 0 : ca.nblk;
+  const int nbk = (int)gridDim.x - nfirst, bk = (int)blockIdx.x - nfirst, nb8 = nbk & ~7;
   const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
   const int chunk = L % nch, cgrp = L / nch;
-  T(*lds_all)[NP * P1 * CWc] = reinterpret_cast<T(*)[NP * P1 * CWc]>(cell_raw);
+  // (of a size known here where no chain shares it: the compiler then knows the waves that fit)
+  constexpr bool own = FIRST != CellFirst::chain;
+  __shared__ T lds_own[own ? 4 : 1][own ? NP * P1 * CWc : 1], wv_own[own ? 4 : 1][own ? 128 : 1];
+  T(*lds_all)[NP * P1 * CWc] = reinterpret_cast<T(*)[NP * P1 * CWc]>(own ? (void*)lds_own : (void*)cell_raw);
   // W V of the wave's cell at its quadrature points
-  T(*wv_all)[128] = reinterpret_cast<T(*)[128]>(cell_raw + 4 * sizeof(lds_all[0]));
+  T(*wv_all)[128] = reinterpret_cast<T(*)[128]>(own ? (void*)wv_own : (void*)(cell_raw + 4 * sizeof(lds_all[0])));
   const KP<T>& P = kb.k[blockIdx.z];
   const int ncr = P.ncr;
   if (chunk * CWc >= ncr) return;  // column block beyond this operator's width
@@ -2398,17 +2406,23 @@ void launch_cell_lanes(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, hi
   constexpr int CWc = lanes_cw<P1>();
   const int nch = (int)cdiv(max_ncr, CWc);
   dim3 grid((unsigned)(cdiv(op->n_cells, 4) * nch + ca.nblk), 1, (unsigned)kb.nk);
-  const size_t lds = std::max(cell_lanes_lds_bytes<T, P1>(),
-                              ca.nblk && !ca.zo_only ? enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell) : (size_t)0);
+  const bool chain = ca.nblk && !ca.zo_only;
+  const size_t lds =
+      chain ? std::max(cell_lanes_lds_bytes<T, P1>(), enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell)) : (size_t)0;
+  auto go = [&](auto none, auto zo, auto with_chain) {
+    hipLaunchKernelGGL(chain ? with_chain : ca.nblk ? zo : none, grid, dim3(256), lds, s, kb, coef<T>(op), op->nc, op->p,
+                       op->n, op->n_cells, nch, ca);
+  };
+  using F = CellFirst;
   if constexpr (CPLX) {
     if (op->uform) {  // the operators of a batch share the form (checked by the batched entry points)
-      hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, true, true>), grid, dim3(256), lds, s, kb, coef<T>(op), op->nc,
-                         op->p, op->n, op->n_cells, nch, ca);
+      go(&fe_cell_lanes_kernel<T, P1, true, true, F::none>, &fe_cell_lanes_kernel<T, P1, true, true, F::zo>,
+         &fe_cell_lanes_kernel<T, P1, true, true, F::chain>);
       return;
     }
   }
-  hipLaunchKernelGGL((fe_cell_lanes_kernel<T, P1, CPLX>), grid, dim3(256), lds, s, kb, coef<T>(op), op->nc, op->p, op->n,
-                     op->n_cells, nch, ca);
+  go(&fe_cell_lanes_kernel<T, P1, CPLX, false, F::none>, &fe_cell_lanes_kernel<T, P1, CPLX, false, F::zo>,
+     &fe_cell_lanes_kernel<T, P1, CPLX, false, F::chain>);
 }
 
 // The planes-in-lanes kernel forms row offsets within a z-plane of X and of the node-slot
@@ -2430,16 +2444,23 @@ bool lanes_offsets_fit(const oefe_op_s* op, const KBatch<T>& kb) {
 // 0.34 M 36.9 -> 30.2 (float32 42.5 -> 25.1), 1.6 M 47.1 -> 42.9, 4.1 M 87.0 -> 82.1, 8.0 M 169.2 -> 168.0
 // (float32 98.7 -> 96.6); four k-points of 17 M elements each 1703 -> 1726 and 1880 -> 1953
 // (periodic-function form): there the fold, not the waits, is what the side stream hides.
+// Every cell workgroup of such a launch holds the chain's LDS and registers (complex128 degree 2: 108 for 64).
+// One complex128 k-point of eight atoms, 16 / 24 / 32 functions (three workgroups a CU or more): degree 2,
+// 1.0 M elements 52 -> 47 and 3.1 M 92 -> 91; degree 4, 5.3 M 124 -> 117 and 8.2 M 226 -> 222.  With 40
+// functions (59 KB of LDS: two workgroups a CU): degree 2, 0.44 M 48 -> 38, 1.0 M 59 -> 60, 1.8 M 66 -> 70;
+// degree 3, 0.66 M 47 -> 41, 1.0 M 54 -> 55, 1.8 M 60 -> 67; degree 4, 0.70 M 49 -> 47, 3.5 M 115 -> 117.
+// Complex64 (29 KB): never slower up to 8 M.
 template <typename T, bool CPLX>
 bool chain_in_cell(const oefe_op_s* op, const KBatch<T>& kb, bool bf16) {
   if (bf16 || op->n_enr < 1 || (op->tune_cw != 0 && !op->uform) || !lanes_offsets_fit(op, kb)) return false;
-  if (enr_chain_lds_bytes<T, CPLX>(op->n_enr, kChainColsCell) > 64 * 1024) return false;
+  const size_t lds = enr_chain_lds_bytes<T, CPLX>(op->n_enr, kChainColsCell);
+  if (lds > 64 * 1024) return false;
   int64_t elems = 0;
   for (int q = 0; q < kb.nk; ++q) {
     if (kb.k[q].nv < 2) return false;  // one column folds its partials in another order
     elems += op->N * kb.k[q].ncr;
   }
-  return elems <= kChainInCellElems;
+  return elems <= (3 * lds <= 160 * 1024 ? kChainInCellElems : kChainInCellElemsLarge);
 }
 
 // cw = 0: planes-in-lanes kernel; 8, 16, 32, 64: plane-per-wave kernel with cw columns per cell

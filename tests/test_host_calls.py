@@ -52,3 +52,27 @@ def test_failed_node_launch_leaves_no_side_work(rec, m):
     joined = [i for i, e in enumerate(ev) if type(e).__name__ == "Record" and e.stream == ev[side[-1]].stream and i > side[-1]]
     assert joined and any(type(e).__name__ == "Wait" and e.stream == 7 and e.event == ev[joined[-1]].event
                           for e in ev[joined[-1]:])
+
+
+def _launches(ev, name):
+    return [e for e in ev if type(e).__name__ == "Launch" and name in e.kernel]
+
+
+@pytest.mark.parametrize("nc,nv,nfn,in_cell", [(8, 16, 5, True), (12, 64, 5, False), (12, 64, 3, True)])
+def test_chain_in_cell_launch_of_a_bloch_operator(rec, nc, nv, nfn, in_cell):
+    """Where a complex128 step's enrichment chain runs.  As the first blocks of the cell launch it holds that
+    launch's LDS and registers, which 40 functions (59 KB, two workgroups a CU) may do for a small step only:
+    a step of 1.8 M elements takes the side stream, and its cell kernel is the instance without the chain."""
+    enr = [wl.EnrichmentFn(a, i // 4, 14.0 / (1 + i % 4), (i % 4) - 1) for a in range(8) for i in range(nfn)]
+    s = dataclasses.replace(wl.diamond8(nc=nc, p=2), enr=enr).with_k(np.array([0.21, -0.37, 0.13]))
+    op = rec.operator(s)
+    rec.events()
+    assert rec.filter(op, C128, s.n_tot, nv, 4) == 0
+    ev = rec.events()
+    cells = _launches(ev, "fe_cell_lanes_kernel")
+    assert len(cells) == 4 and all(c.stream == 7 for c in cells)
+    assert bool([e for e in ev if type(e).__name__ == "Launch" and e.stream != 7]) == (not in_cell)
+    for c in cells:
+        # workgroups of 256 threads by LDS: the cell tile's 21 KB (static, 0 here) or the chain's
+        assert (c.lds == 0) == (not in_cell)
+    assert len({c.kernel for c in cells}) == 1
