@@ -551,23 +551,36 @@ __device__ __forceinline__ void enr_chain(const KBatch<T>& kb, const ChainArgs& 
     // every function has at most kReduceChunk partials: folded here, in the order of enr_reduce1_kernel
     for (int t = tid; t < n * TC; t += nth) {
       const int i = t / TC, jl = t - i * TC, j = min(j0 + jl, m - 1);
+      // entry e of the list: group e mod 4, its even or odd entries; 8 entries at a time, their loads together
+      // and the next positions beside them.  One by one, each entry is two dependent loads: with 27 partials of
+      // each of 40 functions an application to 16 vectors takes 39.7 us so, 29.9 in batches.
       const int e0 = fn_pptr[i], cnt = fn_pptr[i + 1] - e0;
+      const T* pj = P.part + (int64_t)j * E;
+      T r[8] = {}, q[8] = {};
+      int off[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) off[u] = cnt > 0 ? fn_poff[e0 + min(u, cnt - 1)] : 0;
+      for (int e = 0; e < cnt; e += 8) {
+        T v[8], w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const T* p = pj + (int64_t)off[u] * ncr;
+          v[u] = p[0];
+          w[u] = CPLX ? p[E - 1] : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) off[u] = fn_poff[e0 + min(e + 8 + u, cnt - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {  // (an entry past the list is left out, not added as a product with 0)
+          r[u] = e + u < cnt ? r[u] + v[u] : r[u];
+          if (CPLX) q[u] = e + u < cnt ? q[u] + w[u] : q[u];
+        }
+      }
       T wr[4], wi[4];
 #pragma unroll
       for (int grp = 0; grp < 4; ++grp) {
-        T r[2] = {0, 0}, q[2] = {0, 0};  // even and odd entries of the group
-        for (int k = 0; grp + 4 * k < cnt; ++k) {
-          const T* v = P.part + (int64_t)fn_poff[e0 + grp + 4 * k] * ncr + (int64_t)j * E;
-          if (k & 1) {
-            r[1] += v[0];
-            if (CPLX) q[1] += v[1];
-          } else {
-            r[0] += v[0];
-            if (CPLX) q[0] += v[1];
-          }
-        }
-        wr[grp] = r[0] + r[1];
-        wi[grp] = q[0] + q[1];
+        wr[grp] = r[grp] + r[grp + 4];
+        wi[grp] = q[grp] + q[grp + 4];
       }
       T sr, si;
       dot(Hs, Zs, i, jl, sr, si);
