@@ -76,3 +76,15 @@ def test_chain_in_cell_launch_of_a_bloch_operator(rec, nc, nv, nfn, in_cell):
         # workgroups of 256 threads by LDS: the cell tile's 21 KB (static, 0 here) or the chain's
         assert (c.lds == 0) == (not in_cell)
     assert len({c.kernel for c in cells}) == 1
+
+
+@pytest.mark.parametrize("nc,nv,groups", [(6, 16, 1), (12, 8, 1), (12, 72, 2), (12, 320, 4)])
+def test_node_workgroups_of_small_launches(rec, nc, nv, groups):
+    """Column groups of a node workgroup (two waves each) by the size of the launch: 27 tiles of one group and 216
+    of one would leave most CUs idle with workgroups of four, 216 tiles of five groups with workgroups of four."""
+    s = wl.diamond8(nc=nc, p=2)
+    op = rec.operator(s)
+    rec.events()
+    assert rec.filter(op, F64, s.n_tot, nv, 2) == 0
+    nodes = _launches(rec.events(), "fe_node_kernel")
+    assert [e.block for e in nodes] == [128 * groups] * 2
