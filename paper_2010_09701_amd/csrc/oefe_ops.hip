@@ -2067,7 +2067,12 @@ __global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, ChainArgs
 // S and H^oo from memory.  enr_chain_kernel, laid out for 16 columns, computes each sum 16 times over and
 // stages both matrices first: 12.3 us for 64 functions, 7.0 so.  With npq also x . out, from the node
 // workgroups' partials and the enrichment rows.
-constexpr int kCol1ChainMax = 4096;
+// One workgroup reads both matrices, so that beyond kCol1Functions small_gemm's many workgroups are faster, and so
+// is its Z^O (one thread a row of S, in the cell launch, reads no two neighbouring entries).  Microseconds of an
+// application to one column, this chain and Z^O in the cell launch -> small_gemm for both: auxiliary potential
+// of 64 atoms 35 -> 25 this way, of 125 40 -> 33, 216 51.5 -> 50.6, but 343 65 -> 86 and 512 102 -> 168; Kohn-Sham operators of 128
+// functions 48 -> 39, 320 92 -> 108.
+constexpr int kCol1Functions = 256;
 template <typename T>
 __global__ __launch_bounds__(1024) void enr_col1_kernel(KBatch<T> kb, int64_t N, int n,
                                                         const int32_t* __restrict__ fn_pptr,
@@ -2616,7 +2621,7 @@ void launch_cell_bf16(const oefe_op_s* op, const KBatch<float>& kb, hipStream_t 
 // kernel and the chain in one launch.
 bool pq_in_step(const oefe_op_s* op) {
   return !op->cplx && !op->diagonal && op->n_enr > 0 && op->tile_fpmax <= kCol1MaxFunctions &&
-         op->n_enr <= kCol1ChainMax;
+         op->n_enr <= kCol1Functions;
 }
 int64_t pq_partials(const oefe_op_s* op) { return cdiv(tile_count(op->n, op->tile_mode), 4); }
 
@@ -2666,9 +2671,9 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
       nO > 0 && clds <= 96 * 1024 &&
       allow_dynamic_lds(reinterpret_cast<const void*>(&enr_chain_kernel<T, CPLX>), clds) == hipSuccess;
   // few partials per function (small meshes): the chain folds them itself, one launch fewer
-  const bool direct = (one_chain || (!CPLX && !ovl && max_nv == 1 && nO <= kCol1ChainMax)) && op->fn_smax <= kReduceChunk;
+  const bool direct = (one_chain || (!CPLX && !ovl && max_nv == 1 && nO <= kCol1Functions)) && op->fn_smax <= kReduceChunk;
   const bool pq = kb.k[0].pq != nullptr;
-  const bool col1_chain = !CPLX && !ovl && max_nv == 1 && nO > 0 && nO <= kCol1ChainMax;
+  const bool col1_chain = !CPLX && !ovl && max_nv == 1 && nO > 0 && nO <= kCol1Functions;
   if (pq && !(col1_chain && pq_in_step(op))) return OEFE_EINVAL;
   // fold of the tile partials, and the chain that forms W' from it and writes the enrichment rows of
   // out (and, in an overlapped recurrence, Z^O of the next step), on stream se
@@ -2703,7 +2708,7 @@ int apply_step_batch_impl(const oefe_op_s* const* ops, const KBatch<T>& kb, hipS
   int rc = OEFE_OK;
   // outside a recurrence Z^O is formed by the first blocks of the cell launch (of the two kernels that
   // take them): one launch fewer, 25.1 -> 22.8 us for the application to one atom's 8 vectors
-  const bool zo_in_cell = nO > 0 && !ovl && !bf16 &&
+  const bool zo_in_cell = nO > 0 && !ovl && !bf16 && (max_nv > 1 || nO <= kCol1Functions) &&
                           ((!CPLX && max_ncr == 1) || op->uform || (op->tune_cw == 0 && lanes_offsets_fit(op, kb)));
   if (zo_in_cell) {
     const int nblk = (int)cdiv((int64_t)nO * max_nv, 256);

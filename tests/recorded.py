@@ -99,3 +99,9 @@ class Recorded:
         rc = self.lib.oefe_autotune(nk, H, prec, X, LD, NV, reps, work.ctypes.data_as(ctypes.c_void_p), ctypes.byref(cw),
                                     ctypes.byref(cb), ctypes.byref(ms), ctypes.c_void_p(stream))
         return rc, cw.value, cb.value
+
+    def apply(self, h, prec, n_tot, nv, stream=7):
+        x, y = np.ones((n_tot, nv, 2)), np.ones((n_tot, nv, 2))
+        work = np.zeros(int(self.lib.oefe_work_size(h, prec, nv)) + 256, dtype=np.uint8)
+        p = [a.ctypes.data_as(ctypes.c_void_p) for a in (x, y, work)]
+        return self.lib.ham_apply(h, prec, p[0], p[1], ctypes.c_int64(nv), nv, p[2], ctypes.c_void_p(stream))

@@ -89,3 +89,18 @@ def test_node_workgroups_of_small_launches(rec, nc, nv, groups):
     assert rec.filter(op, F64, s.n_tot, nv, 2) == 0
     nodes = _launches(rec.events(), "fe_node_kernel")
     assert [e.block for e in nodes] == [128 * groups] * 2
+
+
+@pytest.mark.parametrize("atoms,one_workgroup", [(250, True), (260, False)])
+def test_one_column_of_many_functions(rec, atoms, one_workgroup):
+    """One workgroup forms the enrichment rows of a column up to 256 functions; beyond, reading both matrices alone
+    takes it longer than the launches of many workgroups."""
+    g = (np.arange(7) + 0.5) * 3.0
+    pos = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)[:atoms]
+    s = wl.System("lattice", 21.0, 10, 2, pos, np.full(atoms, 3.0), 0.5, 0.8, 1.4, [])
+    op = rec.operator(s, poisson=True)
+    rec.events()
+    assert rec.apply(op, F64, s.n_fe + atoms, 1) == 0
+    ev = rec.events()
+    assert bool(_launches(ev, "enr_col1_kernel")) == one_workgroup
+    assert bool(_launches(ev, "small_gemm_kernel")) == (not one_workgroup)
