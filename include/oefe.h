@@ -249,7 +249,7 @@ int oefe_set_launch_shape(oefe_op op, int32_t cw, int32_t cb);
 /* Autotuner of the launch shape for a batch of operators (nk >= 1, same rules
  * as chebyshev_filter_batched).  Times `reps` batched recurrence steps on
  * copies of the blocks X[q] for each cw in {0, 8, 16, 32, 64} and cb in
- * {16, 32, 64, 128}, with HIP events on `stream`, and sets the fastest shape on
+ * {16, 32, 64}, with HIP events on `stream`, and sets the fastest shape on
  * every operator.  X is not modified.  work: oefe_batched_work_size(nk, ops,
  * prec, nv) bytes.  Outputs (host, may be NULL): the chosen cw, cb and the
  * time of one batched step in ms.  Synchronizes the stream. */

@@ -104,3 +104,27 @@ def test_one_column_of_many_functions(rec, atoms, one_workgroup):
     ev = rec.events()
     assert bool(_launches(ev, "enr_col1_kernel")) == one_workgroup
     assert bool(_launches(ev, "small_gemm_kernel")) == (not one_workgroup)
+
+
+@pytest.mark.parametrize("nc", [3, 12])
+def test_autotuner_times_the_steps_of_a_filter(rec, nc):
+    """The launch-shape tuner times steps like those in the middle of a filter, whose node kernel forms the next
+    step's partials: between its timing events no start-up work of a recurrence (partials of the given block,
+    Z^O) is queued, and a shape is timed once."""
+    s = wl.diamond8(nc=nc, p=2) if nc > 3 else wl.tiny_system(nc=nc, p=2, n_atoms=2, seed=13, L=6.0, r0=1.0, r1=2.3)
+    op = rec.operator(s)
+    rec.events()
+    rc, cw, cb = rec.autotune([op], F64, s.n_tot, 40, reps=5)
+    assert rc == 0 and cw in (0, 8, 16, 32, 64) and cb in (16, 32, 64)
+    ev = rec.events()
+    # the events recorded on the stream that no stream waits for are the timing events, in pairs
+    waited = {e.event for e in ev if type(e).__name__ == "Wait"}
+    marks = [i for i, e in enumerate(ev) if type(e).__name__ == "Record" and e.stream == 7 and e.event not in waited]
+    assert len(marks) == 2 * 5 * 3
+    shapes = set()
+    for a, b in zip(marks[::2], marks[1::2]):
+        nodes, cells = _launches(ev[a:b], "fe_node_kernel"), _launches(ev[a:b], "fe_cell")
+        assert len(nodes) == 5 and not _launches(ev[a:b], "fe_part_kernel")
+        assert all("ELi1ELb0EEEv" in n.kernel for n in nodes)  # partials from the result, not from the step's X
+        shapes.add((cells[0].kernel, cells[0].grid, nodes[0].block))
+    assert len(shapes) == 15
