@@ -258,7 +258,7 @@ def run_passes(oefe, torch, gop, X, m, dev_bounds, n_warm, n_steps):
 
 def _batched_filter_timing(oefe, torch, ops, blocks, abc, m, reps, work, label):
     """Mean time of `reps` batched filters per precision (complex128, complex64), after the
-    launch-shape autotuner, with the average cell / node / coupling stage times."""
+    launch-shape autotuner, with the average cell and node stage times (the node kernel holds the coupling)."""
     res = {}
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
@@ -274,7 +274,7 @@ def _batched_filter_timing(oefe, torch, ops, blocks, abc, m, reps, work, label):
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1) / reps
         stages = {}
-        for which in ("cell", "node", "coupling"):
+        for which in ("cell", "node"):
             ops[0].kernel_timer(which)
             oefe.chebyshev_filter_batched(ops, Xs, m, abc)
             n_launch, tot_ms = ops[0].kernel_timer_read()
