@@ -500,7 +500,8 @@ int upload_operator(oefe_op_s* op, std::string& err) {
             if (cplx) hkin[o + 1] = B.hkin[r * B.nf + f].imag();
           }
       }
-      // common support cells of every pair of atom blocks (ascending cell index)
+      // common support cells of every pair bi <= bj of atom blocks (ascending cell index); the others' lists
+      // are empty
       std::vector<int64_t> hp_ptr((size_t)nb * nb + 1, 0);
       std::vector<int32_t> hp_i, hp_j;
       for (int bi = 0; bi < nb; ++bi)
@@ -508,7 +509,7 @@ int upload_operator(oefe_op_s* op, std::string& err) {
           auto& ci = op->blocks[bi].cells;
           auto& cj = op->blocks[bj].cells;
           size_t i = 0, j = 0;
-          while (i < ci.size() && j < cj.size()) {
+          while (bi <= bj && i < ci.size() && j < cj.size()) {
             if (ci[i] < cj[j]) { ++i; continue; }
             if (ci[i] > cj[j]) { ++j; continue; }
             hp_i.push_back((int32_t)(boff[bi] + (int64_t)i));

@@ -200,7 +200,7 @@ struct DeviceArrays {
   int32_t* rr_ent = nullptr;    // pair: 128 * (flattened support cell) + local node
   int32_t* cf_cell = nullptr;   // cell of each flattened support cell (index into phi)
   int64_t* csr2tile = nullptr;  // CSR entry -> tile_val position [fr_nnz]
-  int64_t* hp_ptr = nullptr;    // atom-block pair (bi nb + bj) -> common support cells [nb^2 + 1]
+  int64_t* hp_ptr = nullptr;    // atom-block pair (bi nb + bj, bi <= bj) -> common support cells [nb^2 + 1]
   int32_t* hp_i = nullptr;      // flattened support cell of bi for each common cell
   int32_t* hp_j = nullptr;      // flattened support cell of bj
   // auxiliary-potential Poisson operator (oefe_poisson_create)

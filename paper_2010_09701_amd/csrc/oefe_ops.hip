@@ -1870,7 +1870,7 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
   step_scalars(P, alpha, c, beta);
   const T xv = ok ? P.x[(int64_t)g * P.ldx] : T(0);
   const T pv = beta != T(0) ? P.prev[(int64_t)g * P.ldo] : T(0);
-  // slots of the node: (bx + {0, x2}) x (by + {0, y2}) x (bz + {0, z2}), as in the fused kernel
+  // slots of the node: (bx + {0, x2}) x (by + {0, y2}) x (bz + {0, z2}), as in fe_node_kernel
   const int qx = div_p(ix, p), rx = ix - qx * p, qy = div_p(iy, p), ry = iy - qy * p, qz = div_p(iz, p),
             rz = iz - qz * p;
   const int bx = qx * P1 + (rx ? rx + 1 : 0), by = qy * P1 + (ry ? ry + 1 : 0), bz = qz * P1 + (rz ? rz + 1 : 0);
@@ -1899,12 +1899,7 @@ __global__ __launch_bounds__(256) void fe_node_col1_kernel(KBatch<T> kb, int nc,
       T h[4], z[4], q[4];
       __builtin_memcpy(h, __builtin_assume_aligned(tv + fb, 2 * sizeof(T)), sizeof(h));  // (FP, pad and offsets are even)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        // padding entries of the list hold -1 (and zero coupling values): Z^O row 0, replaced by 0
-        const int fn = tile_fns[f0 + fb + i];
-        const T zl = P.zo[(int64_t)max(fn, 0) * P.ncr];
-        z[i] = fn >= 0 ? zl : T(0);
-      }
+      for (int i = 0; i < 4; ++i) z[i] = P.zo[(int64_t)tile_fns[f0 + fb + i] * P.ncr];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         acc = fma(h[i], z[i], acc);
