@@ -1252,8 +1252,10 @@ __global__ __launch_bounds__(768) void fe_cell_bf16_kernel(KBatch<float> kb, con
 // of up to 4 column groups share the tile's coupling block in LDS, copied there without passing
 // through registers, and a table of what each row needs (offsets, factors, flags).  A wave holds its
 // rows in the layout of the 16x16x4 MFMA result (row 16 rb + M::row(lane, v), column lane % 16), so that
-// Ht_t Z^O, slot sums, X, previous iterate and output meet in registers without a transpose; all its
-// loads are issued before the first is used.  In a recurrence the partial is formed from the result,
+// Ht_t Z^O, slot sums, X, previous iterate and output meet in registers without a transpose; the loads of X and
+// of the first slot pairs are issued before the first is used, then those of the previous iterate (in float32
+// behind them; in float64 the test for it is a value per lane to the compiler, so they wait for the earlier
+// ones and go out one by one).  In a recurrence the partial is formed from the result,
 // which is the next step's X: only there are rows exchanged (LDS tile of the column group), each half
 // taking alternate blocks of 16 functions.
 //
@@ -1596,7 +1598,7 @@ __global__ __launch_bounds__(128 * kNodeGroups, 4) void fe_node_kernel(KBatch<T>
   };
   lds_barrier();  // the rows
 
-  // ---- loads of all the wave's rows in one batch (element v of group rb: row 16 rb + M::row(lane, v)):
+  // ---- loads of all the wave's rows (element v of group rb: row 16 rb + M::row(lane, v)):
   // X; the first slot pair of every node, its lower-x slot and, where it is shared in x, the next one
   // (else the first again: in bounds, cached, discarded); the previous iterate (read before any element
   // of out, which may be the same array, is written).  Slot columns past ncr (ldc >= ncr) read the next
