@@ -692,6 +692,10 @@ constexpr size_t cell_lanes_lds_bytes() { return 4 * (P1 * P1 * P1 * lanes_cw<P1
 // FIRST: what the launch's first ca.nblk blocks do instead.  An instance of its own each: the registers of the
 // enrichment chain would be those of every cell block (complex128 degree 2: 64 without it, 108 with it).
 enum class CellFirst { none, zo, chain };
+template <typename T, int P1, bool UF>
+constexpr bool cell_lanes_own_lds(CellFirst first) {
+  return first != CellFirst::chain && !(sizeof(T) == 8 && P1 == 4 && !UF);
+}
 template <typename T, int P1, bool CPLX, bool UF, CellFirst FIRST>
 __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, CellCoef<T> cf, int nc, int p, int n,
                                                             int64_t n_cells, int nch, ChainArgs ca) {
@@ -714,8 +718,10 @@ __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, Cel
   const int nbk = (int)gridDim.x - nfirst, bk = (int)blockIdx.x - nfirst, nb8 = nbk & ~7;
   const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
   const int chunk = L % nch, cgrp = L / nch;
-  // (of a size known here where no chain shares it: the compiler then knows the waves that fit)
-  constexpr bool own = FIRST != CellFirst::chain;
+  // (of a size known here where no chain shares it: the compiler then knows the waves that fit; except in float64
+  // of degree 3, whose waves it would fit into 107 registers with scalar ones spilled, four waves either way: an
+  // application to 90 vectors, 12^3 cells, 101 us so and 94 with 128)
+  constexpr bool own = cell_lanes_own_lds<T, P1, UF>(FIRST);
   __shared__ T lds_own[own ? 4 : 1][own ? NP * P1 * CWc : 1], wv_own[own ? 4 : 1][own ? 128 : 1];
   T(*lds_all)[NP * P1 * CWc] = reinterpret_cast<T(*)[NP * P1 * CWc]>(own ? (void*)lds_own : (void*)cell_raw);
   // W V of the wave's cell at its quadrature points
@@ -2420,22 +2426,24 @@ void launch_cell_lanes(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, hi
   const int nch = (int)cdiv(max_ncr, CWc);
   dim3 grid((unsigned)(cdiv(op->n_cells, 4) * nch + ca.nblk), 1, (unsigned)kb.nk);
   const bool chain = ca.nblk && !ca.zo_only;
-  const size_t lds =
-      chain ? std::max(cell_lanes_lds_bytes<T, P1>(), enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell)) : (size_t)0;
-  auto go = [&](auto none, auto zo, auto with_chain) {
-    hipLaunchKernelGGL(chain ? with_chain : ca.nblk ? zo : none, grid, dim3(256), lds, s, kb, coef<T>(op), op->nc, op->p,
-                       op->n, op->n_cells, nch, ca);
+  auto go = [&](auto uf) {
+    constexpr bool UF = decltype(uf)::value;
+    using F = CellFirst;
+    const size_t tile = cell_lanes_own_lds<T, P1, UF>(F::none) ? 0 : cell_lanes_lds_bytes<T, P1>();  // dynamic LDS
+    const size_t lds =
+        chain ? std::max(cell_lanes_lds_bytes<T, P1>(), enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell)) : tile;
+    auto* kernel = chain     ? &fe_cell_lanes_kernel<T, P1, CPLX, UF, F::chain>
+                   : ca.nblk ? &fe_cell_lanes_kernel<T, P1, CPLX, UF, F::zo>
+                             : &fe_cell_lanes_kernel<T, P1, CPLX, UF, F::none>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, kb, coef<T>(op), op->nc, op->p, op->n, op->n_cells, nch, ca);
   };
-  using F = CellFirst;
   if constexpr (CPLX) {
     if (op->uform) {  // the operators of a batch share the form (checked by the batched entry points)
-      go(&fe_cell_lanes_kernel<T, P1, true, true, F::none>, &fe_cell_lanes_kernel<T, P1, true, true, F::zo>,
-         &fe_cell_lanes_kernel<T, P1, true, true, F::chain>);
+      go(std::true_type{});
       return;
     }
   }
-  go(&fe_cell_lanes_kernel<T, P1, CPLX, false, F::none>, &fe_cell_lanes_kernel<T, P1, CPLX, false, F::zo>,
-     &fe_cell_lanes_kernel<T, P1, CPLX, false, F::chain>);
+  go(std::false_type{});
 }
 
 // The planes-in-lanes kernel forms row offsets within a z-plane of X and of the node-slot
