@@ -2469,8 +2469,8 @@ bool lanes_offsets_fit(const oefe_op_s* op, const KBatch<T>& kb) {
 // One complex128 k-point of eight atoms, 16 / 24 / 32 functions (three workgroups a CU or more): degree 2,
 // 1.0 M elements 52 -> 47 and 3.1 M 92 -> 91; degree 4, 5.3 M 124 -> 117 and 8.2 M 226 -> 222.  With 40
 // functions (59 KB of LDS: two workgroups a CU): degree 2, 0.44 M 48 -> 38, 1.0 M 59 -> 60, 1.8 M 66 -> 70;
-// degree 3, 0.66 M 47 -> 41, 1.0 M 54 -> 55, 1.8 M 60 -> 67; degree 4, 1.1 M 55 -> 52, 1.6 M 72 -> 72.5, 3.5 M
-// 115 -> 117, 8.2 M 261 -> 265.
+// degree 3, 0.66 M 47 -> 41, 1.0 M 54 -> 55, 1.8 M 60 -> 67; degree 4, 1.1 M 55 -> 52, 1.6 M 72 -> 72.5, 2.0 M
+// 70 -> 61, 2.8 M 84 -> 81, 3.5 M 115 -> 117, 5.3 M 145 -> 142, 8.2 M 261 -> 265.
 // Complex64 (29 KB): never slower up to 8 M.
 template <typename T, bool CPLX>
 bool chain_in_cell(const oefe_op_s* op, const KBatch<T>& kb, bool bf16) {
@@ -2482,8 +2482,8 @@ bool chain_in_cell(const oefe_op_s* op, const KBatch<T>& kb, bool bf16) {
     if (kb.k[q].nv < 2) return false;  // one column folds its partials in another order
     elems += op->N * kb.k[q].ncr;
   }
-  // (two workgroups a CU instead of 3, 4 and 7 of degree 4, 3 and 2)
-  return elems <= (3 * lds <= 160 * 1024 ? kChainInCellElems : (int64_t)(op->P1 == 5 ? 6 : 3) << 18);
+  // (two workgroups a CU instead of seven and four of degree 2 and 3; degree 4 has three)
+  return elems <= (op->P1 == 5 || 3 * lds <= 160 * 1024 ? kChainInCellElems : (int64_t)3 << 18);
 }
 
 // cw = 0: planes-in-lanes kernel; 8, 16, 32, 64: plane-per-wave kernel with cw columns per cell
