@@ -2540,10 +2540,10 @@ int launch_node_nc(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRu
   // idle ones.  At equal counts 4 groups share a block in float64 (diamond64, 320 columns: 2930 us
   // against 3560 with 2) and 2 in float32 (1430 against 1480); else the wider of equals.  Small launches take
   // narrower workgroups than that, 2 groups below five workgroups of 4 to four CUs (complex128, whose blocks are
-  // the largest: one to a CU) and 1 below three of 2: a CU then copies fewer blocks before its work can start.
-  // Applications in microseconds with 1, 2 and 4 groups: float64, 216 tiles of 1 group (8 vectors) 32, 33, 35;
-  // 216 x 2 34, 33, 36; 216 x 3 37, 38, 39; 216 x 5 48, 43, 47; 343 x 5 57, 56, 53.  Complex128, 216 x 3 58,
-  // 49, 51; 216 x 5 71, 64, 60.  Complex64, 216 x 1 36.5, 37, 42; 216 x 2 42, 41, 45.
+  // the largest: one to a CU) and 1 where that still is less than a group to a CU: a CU then copies fewer blocks before
+  // its work can start.  Applications in microseconds with 1, 2 and 4 groups: float64, 216 tiles of 1 group
+  // (8 vectors) 32, 33, 35; 92 x 3 30, 29, 33; 216 x 3 37, 38, 39; 216 x 5 48, 43, 47; 343 x 5 57, 56, 53.  Complex128,
+  // 92 x 3 42, 40, 44; 216 x 3 58, 49, 51; 216 x 5 71, 64, 60.  Complex64, 216 x 1 36.5, 37, 42; 216 x 2 42, 41, 45.
   const int G = (int)cdiv(max_ncr, 16 * NC);
   const int fixed = op->tune_cb > 0 ? std::max(1, std::min(kNodeGroups, op->tune_cb / 16)) : 0;
   int64_t items = 0;  // (tile, column group) pairs of the launch
@@ -2551,7 +2551,7 @@ int launch_node_nc(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, NodeRu
   int W = 1;
   double best = 0;
   for (int w : {1, 2, 4}) {
-    if (fixed ? w != (fixed == 3 ? 2 : fixed) : w > 1 && items < (w == 2 ? 384 : CPLX && sizeof(T) == 8 ? 1024 : 1280)) continue;
+    if (fixed ? w != (fixed == 3 ? 2 : fixed) : w > 1 && items < (w == 2 ? 256 : CPLX && sizeof(T) == 8 ? 1024 : 1280)) continue;
     int ntl = 1;
     for (int q = 0; q < kb.nk; ++q) ntl = std::max(ntl, node_tiles((int)cdiv(kb.k[q].ncr, 16 * NC), w));
     for (int span = 0; span < 2; ++span) {
