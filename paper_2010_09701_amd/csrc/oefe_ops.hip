@@ -690,7 +690,7 @@ constexpr size_t cell_lanes_lds_bytes() { return 4 * (P1 * P1 * P1 * lanes_cw<P1
 // the backward passes project.
 //
 // FIRST: what the launch's first ca.nblk blocks do instead.  An instance of its own each: the registers of the
-// enrichment chain would be those of every cell block (complex128 degree 2: 64 without it, 108 with it).
+// enrichment chain would be those of every cell block (complex128 degree 2: 64 without it, 124 with it).
 enum class CellFirst { none, zo, chain };
 template <typename T, int P1, bool UF>
 constexpr bool cell_lanes_own_lds(CellFirst first) {
@@ -2071,10 +2071,10 @@ __global__ __launch_bounds__(1024) void enr_chain_kernel(KBatch<T> kb, ChainArgs
 // stages both matrices first: 12.3 us for 64 functions, 7.0 so.  With npq also x . out, from the node
 // workgroups' partials and the enrichment rows.
 // One workgroup reads both matrices, so that beyond kCol1Functions small_gemm's many workgroups are faster, and so
-// is its Z^O (one thread a row of S, in the cell launch, reads no two neighbouring entries).  Microseconds of an
-// application to one column, this chain and Z^O in the cell launch -> small_gemm for both: auxiliary potential
-// of 64 atoms 35 -> 25 this way, of 125 40 -> 33, 216 51.5 -> 50.6, but 343 65 -> 86 and 512 102 -> 168; Kohn-Sham operators of 128
-// functions 48 -> 39, 320 92 -> 108.
+// is its Z^O (in the cell launch one thread takes a row of S, and no two read neighbouring entries).
+// Microseconds of an application to one column, small_gemm for both -> this chain, and Z^O in the cell launch:
+// auxiliary potential of 64 atoms 35 -> 25, of 125 40 -> 33, 216 51.5 -> 50.6, but 343 65 -> 86 and 512 102 ->
+// 168; Kohn-Sham operators of 128 functions 48 -> 39, of 320 92 -> 108.
 constexpr int kCol1Functions = 256;
 template <typename T>
 __global__ __launch_bounds__(1024) void enr_col1_kernel(KBatch<T> kb, int64_t N, int n,
@@ -2160,7 +2160,9 @@ __global__ void diag_step_kernel(const T* __restrict__ lam, const T* __restrict_
 // takes row tiles w, w + P1, ... of 16 points and all column tiles, its accumulators start from the
 // finite-element values, N^O is read once from memory, and the sum over columns needs 4 shuffles of a point's
 // 16 lanes.  diamond8, 72 columns: 328 -> 163 us, of which the finite-element
-// part of the second, mostly empty block of columns is about a third.
+// part of the second, mostly empty block of columns is about a third.  psi is float64 for float32 blocks too:
+// 66 KB a workgroup for 32 (degree 4), two on a CU for five; the call with 72 float32 columns 346 -> 170 us,
+// 64 columns 181 -> 98, 72 complex64 columns 1086 -> 448.
 // ---------------------------------------------------------------------------
 constexpr int kFnList = 128;  // enrichment functions of a cell listed at a time
 
@@ -2465,7 +2467,7 @@ bool lanes_offsets_fit(const oefe_op_s* op, const KBatch<T>& kb) {
 // 0.34 M 36.9 -> 30.2 (float32 42.5 -> 25.1), 1.6 M 47.1 -> 42.9, 4.1 M 87.0 -> 82.1, 8.0 M 169.2 -> 168.0
 // (float32 98.7 -> 96.6); four k-points of 17 M elements each 1703 -> 1726 and 1880 -> 1953
 // (periodic-function form): there the fold, not the waits, is what the side stream hides.
-// Every cell workgroup of such a launch holds the chain's LDS and registers (complex128 degree 2: 108 for 64).
+// Every cell workgroup of such a launch holds the chain's LDS and registers (complex128 degree 2: 124 for 64).
 // One complex128 k-point of eight atoms, 16 / 24 / 32 functions (three workgroups a CU or more): degree 2,
 // 1.0 M elements 52 -> 47 and 3.1 M 92 -> 91; degree 4, 5.3 M 124 -> 117 and 8.2 M 226 -> 222.  With 40
 // functions (59 KB of LDS: two workgroups a CU): degree 2, 0.44 M 48 -> 38, 1.0 M 59 -> 60, 1.8 M 66 -> 70;
