@@ -1677,8 +1677,9 @@ bool same_layout(const oefe_op_s* a, const oefe_op_s* b) {
          b->poisson == a->poisson && b->tile_pad == a->tile_pad;
 }
 
-// Launch-shape tuner: times the batched steps in the middle of a recurrence (out = alpha (Ht x - c x) - beta out:
-// the filter's kernels, access pattern and stream overlap, bounded values) for each candidate cell-tile
+// Launch-shape tuner: times the batched steps in the middle of a recurrence (out = alpha Ht x - prev, x the
+// result of the step before and out in prev's place: the filter's kernels, access pattern and stream
+// overlap; values stay bounded while alpha times the spectrum is below 2) for each candidate cell-tile
 // width cw and node-stage width cb (1, 2 and 4 column groups: every shape there is), and keeps the
 // fastest on every operator.
 template <typename T>
@@ -1690,7 +1691,7 @@ int autotune_impl(int nk, const oefe_op* ops, bool bf16, void* const* X, const i
   std::vector<T*> outp(nk);
   std::vector<int> nvv(nk);
   std::vector<int64_t> ldp(nk);
-  std::vector<double> al(nk, 1e-3), cc(nk, 0.0), be(nk, 0.5);
+  std::vector<double> al(nk, 1e-5), cc(nk, 0.0), be(nk, 1.0);
   char* p = (char*)work;
   for (int q = 0; q < nk; ++q) {
     const int E = ops[q]->cplx ? 2 : 1;
@@ -1731,7 +1732,12 @@ int autotune_impl(int nk, const oefe_op* ops, bool bf16, void* const* X, const i
         ov.last = last;
         const int e = apply_step_batch<T>(opp, nk, bf16, xin.data(), ldp.data(), pin.data(), outp.data(), ldp.data(),
                                           nvv.data(), al.data(), cc.data(), be.data(), sw.data(), s, &ov);
-        for (int q = 0; q < nk; ++q) std::swap(sw[q].zo, sw[q].zn);
+        for (int q = 0; q < nk; ++q) {
+          std::swap(sw[q].zo, sw[q].zn);
+          pin[q] = xin[q];
+          xin[q] = outp[q];
+          outp[q] = const_cast<T*>(pin[q]);
+        }
         return e;
       };
       // the first step and one like the timed ones (first launches of these instances), then the timed ones,
