@@ -692,9 +692,14 @@ constexpr size_t cell_lanes_lds_bytes() { return 4 * (P1 * P1 * P1 * lanes_cw<P1
 // FIRST: what the launch's first ca.nblk blocks do instead.  An instance of its own each: the registers of the
 // enrichment chain would be those of every cell block (complex128 degree 2: 64 without it, 124 with it).
 enum class CellFirst { none, zo, chain };
+// Whether the LDS is static, of a size the compiler knows: it then fits the registers to the waves that fit.  Not
+// with a chain (its size), and not in float64 where that costs more than it gives: degree 3 would take 107
+// registers with scalar ones spilled, four waves either way (an application to 90 vectors, 12^3 cells, 101 us so
+// and 94 with 128), degree 4 with Z^O 167 for 157, three waves (band energy of 72 vectors 724 us and 722).
 template <typename T, int P1, bool UF>
 constexpr bool cell_lanes_own_lds(CellFirst first) {
-  return first != CellFirst::chain && !(sizeof(T) == 8 && P1 == 4 && !UF);
+  return first != CellFirst::chain &&
+         !(sizeof(T) == 8 && !UF && (P1 == 4 || (P1 == 5 && first == CellFirst::zo)));
 }
 template <typename T, int P1, bool CPLX, bool UF, CellFirst FIRST>
 __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, CellCoef<T> cf, int nc, int p, int n,
@@ -718,9 +723,6 @@ __global__ __launch_bounds__(256, 3) void fe_cell_lanes_kernel(KBatch<T> kb, Cel
   const int nbk = (int)gridDim.x - nfirst, bk = (int)blockIdx.x - nfirst, nb8 = nbk & ~7;
   const int L = bk < nb8 ? (bk & 7) * (nb8 >> 3) + (bk >> 3) : bk;
   const int chunk = L % nch, cgrp = L / nch;
-  // (of a size known here where no chain shares it: the compiler then knows the waves that fit; except in float64
-  // of degree 3, whose waves it would fit into 107 registers with scalar ones spilled, four waves either way: an
-  // application to 90 vectors, 12^3 cells, 101 us so and 94 with 128)
   constexpr bool own = cell_lanes_own_lds<T, P1, UF>(FIRST);
   __shared__ T lds_own[own ? 4 : 1][own ? NP * P1 * CWc : 1], wv_own[own ? 4 : 1][own ? 128 : 1];
   T(*lds_all)[NP * P1 * CWc] = reinterpret_cast<T(*)[NP * P1 * CWc]>(own ? (void*)lds_own : (void*)cell_raw);
@@ -2431,7 +2433,8 @@ void launch_cell_lanes(const oefe_op_s* op, const KBatch<T>& kb, int max_ncr, hi
   auto go = [&](auto uf) {
     constexpr bool UF = decltype(uf)::value;
     using F = CellFirst;
-    const size_t tile = cell_lanes_own_lds<T, P1, UF>(F::none) ? 0 : cell_lanes_lds_bytes<T, P1>();  // dynamic LDS
+    const bool own = ca.nblk ? cell_lanes_own_lds<T, P1, UF>(F::zo) : cell_lanes_own_lds<T, P1, UF>(F::none);
+    const size_t tile = own ? 0 : cell_lanes_lds_bytes<T, P1>();  // dynamic LDS
     const size_t lds =
         chain ? std::max(cell_lanes_lds_bytes<T, P1>(), enr_chain_lds_bytes<T, CPLX>(ca.n, kChainColsCell)) : tile;
     auto* kernel = chain     ? &fe_cell_lanes_kernel<T, P1, CPLX, UF, F::chain>
