@@ -242,8 +242,8 @@ size_t oefe_batched_work_size(int32_t nk, const oefe_op* ops, oefe_prec prec, co
  * plane per wave with cw real columns per cell in a 64-lane tile (64/cw cells).
  * cb (a multiple of 16 up to 128; 0 = built-in) is the width of a workgroup of the
  * node stage in column groups: cb / 16 groups of 16 real columns (float32: 32),
- * of which 1, 2 and 4 are used (3 acts as 2, more as 4; built-in: the widest
- * occupancy).  Results do not depend on the shape. */
+ * of which 1, 2 and 4 are used (3 acts as 2, more as 4; built-in: by occupancy,
+ * narrower for small launches).  Results do not depend on the shape. */
 int oefe_set_launch_shape(oefe_op op, int32_t cw, int32_t cb);
 
 /* Autotuner of the launch shape for a batch of operators (nk >= 1, same rules

@@ -3,7 +3,6 @@ import collections
 import ctypes
 import os
 import subprocess
-import tempfile
 
 import numpy as np
 import pytest
@@ -15,11 +14,10 @@ Wait = collections.namedtuple("Wait", "stream event")
 Record = collections.namedtuple("Record", "stream event")
 
 
-def _library():
+def _library(d):
     objs = [os.path.join(build.ROOT, "_build", os.path.splitext(s)[0] + ".o") for s in build.SOURCES]
     if not all(map(os.path.exists, objs)):
         pytest.skip("objects of the library are not there (run __graft_entry__.build())")
-    d = tempfile.mkdtemp(prefix="oefe_rec_")
     lib, stub = os.path.join(d, "liboefe_rec.so"), os.path.join(os.path.dirname(os.path.abspath(__file__)), "hip_record.cpp")
     # the test runtime's own definitions, whatever else the process has loaded
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-Wno-attributes",
@@ -29,10 +27,11 @@ def _library():
 
 
 class Recorded:
-    def __init__(self):
+    def __init__(self, d):
+        """d: a directory for the library"""
         from paper_2010_09701_amd import oefe
         self.desc = oefe._Desc
-        self.lib = _library()
+        self.lib = _library(d)
         self.lib.rec_log.restype = ctypes.c_char_p
         for f in ("oefe_work_size", "oefe_batched_work_size"):
             getattr(self.lib, f).restype = ctypes.c_size_t

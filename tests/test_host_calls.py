@@ -11,9 +11,9 @@ EINVAL = -1
 
 
 @pytest.fixture(scope="module")
-def rec():
+def rec(tmp_path_factory):
     from recorded import Recorded
-    return Recorded()
+    return Recorded(str(tmp_path_factory.mktemp("recorded")))
 
 
 def test_batch_of_unlike_operators_is_refused(rec):
